@@ -1,5 +1,7 @@
 // Causal grouped-query attention of a set of rows over a KV cache, bf16 MFMA,
-// head_dim 128.
+// head_dim HD = 128 or 64 (64-wide heads: 32 query / 8 kv heads, a 1237-token
+// prefill 2814 -> 53 us per layer against one wavefront per row and head, a
+// 48-row repair at position 611 about 600 -> 6 us).
 //
 // A work item is (document, kv head, up to 16*MT consecutive rows of that
 // document, key range [k0, k1)).  The G = Hq/Hkv query heads sharing the kv
@@ -39,15 +41,8 @@ namespace kvr {
 
 namespace {
 
-constexpr int HD = ATT_HD;
 constexpr int KT = ATT_KT;
 constexpr int WAVES = 8;           // wavefronts per block
-constexpr int NLD = 16 / WAVES;    // 16-byte K (and V) loads per thread per tile
-constexpr int KS_STRIDE = HD + 8;   // key tile row stride (bf16): rows 4 banks apart, so the 16
-                                    // rows of a key fragment read fall on distinct banks
-constexpr int VS_STRIDE = HD + 16;  // value tile row stride: rows 8 banks apart, so the four rows
-                                    // a transposing read takes per 16 lanes fall on distinct banks
-constexpr int PART_ROW = HD + 4;   // floats per (head, row) partial: O[128], m, l
 constexpr float RESCALE_SLACK = 8.0f;  // log2 headroom before the running max is raised
 constexpr int COMBINE_NP = 16;         // partials per row loaded in one round by the combine
 
@@ -85,13 +80,24 @@ __device__ __forceinline__ float xsum4(float v) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// PPW: (head, row tile) pairs per wavefront; MT: row tiles of a full item.
-template <int PPW, int KG>
+// HD: head_dim; PPW: (head, row tile) pairs per wavefront; MT: row tiles of a
+// full item.
+template <int HD, int PPW, int KG>
 __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t *Q, const bf16_t *Q_lo,
                                                                     const RowInfo *rows,
                                                                     const AttnItem *items, int layer, int Hq, int Hkv,
                                                                     int MT, float *part, bf16_t *O, bf16_t *O_lo,
                                                                     int o_perm, float *lse) {
+    constexpr int KSTEPS = HD / 32, DTILES = HD / 16;  // k-steps of a score, 16-wide dimension tiles
+    constexpr int CPR = HD / 8;                        // 16-byte chunks per cache row
+    constexpr int NLD = KT * CPR / (64 * WAVES);       // 16-byte K (and V) loads per thread per tile
+    static_assert(HD % 32 == 0 && NLD * 64 * WAVES == KT * CPR, "tile loads");
+    // key tile row stride (bf16): rows 4 banks apart (64-wide heads: 36), so
+    // the 16 rows of a key fragment read fall on distinct banks; value tile:
+    // rows 8 banks apart (40), so the four rows a transposing read takes per
+    // 16 lanes fall on distinct banks
+    constexpr int KS_STRIDE = HD + 8, VS_STRIDE = HD + 16;
+    constexpr int PART_ROW = HD + 4;  // floats per (head, row) partial: O[HD], m, l
     // KG 64-key K tiles, then KG V tiles (one per key group); after the key
     // loop the same memory takes the second key group's softmax state
     __shared__ __attribute__((aligned(16))) bf16_t kv_lds[KG * KT * (KS_STRIDE + VS_STRIDE)];
@@ -117,8 +123,8 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
     // this wavefront's pairs: p = w + WAVES*i -> head t = p / MTi, row tile p % MTi
     bool pvalid[PPW];
     int pt[PPW], pm[PPW], prow[PPW];
-    bf16x8 qv[PPW][4], ql[PPW][4];
-    f32x4 oacc[PPW][8];
+    bf16x8 qv[PPW][KSTEPS], ql[PPW][KSTEPS];
+    f32x4 oacc[PPW][DTILES];
     float m[PPW], l[PPW];
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {
@@ -131,12 +137,12 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
         const int qrow = it.row0 + min(r, it.nrows - 1);
         const int j = it.kvh * G + pt[i];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
+        for (int ks = 0; ks < KSTEPS; ++ks) {
             qv[i][ks] = ld16(Q + (size_t)qrow * qd + j * HD + ks * 32 + 8 * g);
             ql[i][ks] = ld16(Q_lo + (size_t)qrow * qd + j * HD + ks * 32 + 8 * g);
         }
 #pragma unroll
-        for (int nt = 0; nt < 8; ++nt) oacc[i][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int nt = 0; nt < DTILES; ++nt) oacc[i][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
         m[i] = -INFINITY;
         l[i] = 0.f;
     }
@@ -148,10 +154,10 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
 #define KVR_ATT_FETCH(kb_)                                                                                  \
     _Pragma("clang loop unroll(full)") for (int q = 0; q < KG; ++q) {                                       \
         _Pragma("clang loop unroll(full)") for (int i = 0; i < NLD; ++i) {                                 \
-            /* K and V: key (tid + 64*WAVES*i)/16 of tile q, dims (tid%16)*8 */                             \
-            const int ksrc = min((kb_) + q * KT + ((tid + 64 * WAVES * i) >> 4), it.k1 - 1);                \
-            kreg[q][i] = *reinterpret_cast<const u32x4 *>(Kg + (size_t)ksrc * HD + (tid & 15) * 8);         \
-            vreg[q][i] = *reinterpret_cast<const u32x4 *>(Vg + (size_t)ksrc * HD + (tid & 15) * 8);         \
+            /* K and V: key (tid + 64*WAVES*i)/CPR of tile q, dims (tid%CPR)*8 */                           \
+            const int ksrc = min((kb_) + q * KT + (tid + 64 * WAVES * i) / CPR, it.k1 - 1);                 \
+            kreg[q][i] = *reinterpret_cast<const u32x4 *>(Kg + (size_t)ksrc * HD + (tid % CPR) * 8);        \
+            vreg[q][i] = *reinterpret_cast<const u32x4 *>(Vg + (size_t)ksrc * HD + (tid % CPR) * 8);        \
         }                                                                                                   \
     }
     KVR_ATT_FETCH(it.k0)
@@ -161,9 +167,9 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
         for (int q = 0; q < KG; ++q) {
 #pragma clang loop unroll(full)
             for (int i = 0; i < NLD; ++i) {
-                const int key = q * KT + ((tid + 64 * WAVES * i) >> 4);
-                *reinterpret_cast<u32x4 *>(&Ks[key * KS_STRIDE + (tid & 15) * 8]) = kreg[q][i];
-                *reinterpret_cast<u32x4 *>(&Vs[key * VS_STRIDE + (tid & 15) * 8]) = vreg[q][i];
+                const int key = q * KT + (tid + 64 * WAVES * i) / CPR;
+                *reinterpret_cast<u32x4 *>(&Ks[key * KS_STRIDE + (tid % CPR) * 8]) = kreg[q][i];
+                *reinterpret_cast<u32x4 *>(&Vs[key * VS_STRIDE + (tid % CPR) * 8]) = vreg[q][i];
             }
         }
         __syncthreads();
@@ -192,14 +198,14 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
             for (int nt = 0; nt < 4; ++nt) s[i][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int n0 = 0; n0 < 4; n0 += NTH) {
-            bf16x8 kb[NTH][4];
+            bf16x8 kb[NTH][KSTEPS];
 #pragma unroll
             for (int nt = 0; nt < NTH; ++nt)
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
+                for (int ks = 0; ks < KSTEPS; ++ks)
                     kb[nt][ks] = ld16(&Kt[((n0 + nt) * 16 + (lane & 15)) * KS_STRIDE + ks * 32 + 8 * g]);
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
+            for (int ks = 0; ks < KSTEPS; ++ks)
 #pragma unroll
                 for (int i = 0; i < PPW; ++i) {
                     if (!pvalid[i]) continue;
@@ -240,7 +246,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
                 m[i] = mnew;
                 l[i] *= corr;
 #pragma unroll
-                for (int nt = 0; nt < 8; ++nt) oacc[i][nt] *= corr;
+                for (int nt = 0; nt < DTILES; ++nt) oacc[i][nt] *= corr;
             }
             const float muse = m[i] == -INFINITY ? 0.f : m[i];
             float rs = 0.f;
@@ -272,9 +278,9 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
         // same key slots; as above, the fragments are read first (half of them
         // at a time with two pairs per wavefront, for the same reason) and the MFMAs of the
         // accumulators then interleave (same per-accumulator order)
-        constexpr int NVH = PPW == 1 ? 8 : 4;  // value fragments' column tiles held at once
+        constexpr int NVH = PPW == 1 ? DTILES : 4;  // value fragments' column tiles held at once
 #pragma unroll
-        for (int n0 = 0; n0 < 8; n0 += NVH) {
+        for (int n0 = 0; n0 < DTILES; n0 += NVH) {
             bf16x8 va[NVH][2];
 #pragma unroll
             for (int nt = 0; nt < NVH; ++nt)
@@ -308,9 +314,9 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
 #undef KVR_ATT_FETCH
 
     if constexpr (KG == 2) {
-        // the second key group hands its state (per lane: O^T 32 values, m, l)
+        // the second key group hands its state (per lane: O^T HD/4 values, m, l)
         // to the wavefront of the first group that holds the same pairs
-        constexpr int ST = 34;
+        constexpr int ST = HD / 4 + 2;
         static_assert(WG * PPW * 64 * ST * 4 <= KG * KT * (KS_STRIDE + VS_STRIDE) * 2, "merge area");
         float *mg = reinterpret_cast<float *>(kv_lds);
         __syncthreads();  // every wavefront is done with the K/V tiles
@@ -319,11 +325,11 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
             for (int i = 0; i < PPW; ++i) {
                 float *q = mg + ((lw * PPW + i) * 64 + lane) * ST;
 #pragma unroll
-                for (int nt = 0; nt < 8; ++nt)
+                for (int nt = 0; nt < DTILES; ++nt)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) q[nt * 4 + e] = oacc[i][nt][e];
-                q[32] = m[i];
-                q[33] = l[i];
+                q[ST - 2] = m[i];
+                q[ST - 1] = l[i];
             }
         }
         __syncthreads();
@@ -331,14 +337,14 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
             const float *q = mg + ((lw * PPW + i) * 64 + lane) * ST;
-            const float m1 = q[32], l1 = q[33];
+            const float m1 = q[ST - 2], l1 = q[ST - 1];
             const float M = fmaxf(m[i], m1);
             const float a0 = m[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[i] - M);
             const float a1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - M);
             m[i] = M;
             l[i] = l[i] * a0 + l1 * a1;
 #pragma unroll
-            for (int nt = 0; nt < 8; ++nt)
+            for (int nt = 0; nt < DTILES; ++nt)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) oacc[i][nt][e] = oacc[i][nt][e] * a0 + q[nt * 4 + e] * a1;
         }
@@ -357,7 +363,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
             const float inv = 1.0f / l[i];
             const int r = it.row0 + ri;
 #pragma unroll
-            for (int nt = 0; nt < 8; ++nt) {
+            for (int nt = 0; nt < DTILES; ++nt) {
                 const int c = j * HD + nt * 16 + 4 * g;  // 4 consecutive columns, 8-byte aligned
                 const size_t off = o_perm ? perm_offset(r, c, qd) : (size_t)r * qd + c;
                 uint32_t hi[2], lo[2];
@@ -376,33 +382,34 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
         } else {
             float *p = part + ((size_t)(it.part * G + t) * rows_item + ri) * PART_ROW;
 #pragma unroll
-            for (int nt = 0; nt < 8; ++nt) *reinterpret_cast<f32x4 *>(p + nt * 16 + 4 * g) = oacc[i][nt];
+            for (int nt = 0; nt < DTILES; ++nt) *reinterpret_cast<f32x4 *>(p + nt * 16 + 4 * g) = oacc[i][nt];
             if (g == 0) { p[HD] = m[i]; p[HD + 1] = l[i]; }
         }
     }
 }
 
-// One wavefront per (combine item, query head of the group, two rows): each
-// half-wavefront takes one row, a lane four consecutive head dimensions.  The
-// split partials of the row are merged with log-sum-exp weights (exp2
-// domain), the parts summed in ascending order.  With at most NP parts every
-// partial of the row is loaded in one round (clamped indexes, so the loads
-// are unconditional and all in flight together); longer lists take batches
-// of NP.  `lse` as above.
-template <int NP>
+// One wavefront per (combine item, query head of the group, 256 / HDP rows): a
+// lane takes four consecutive dimensions of one row (HDP is the partial rows'
+// width: head_dim, or the width the generic kernel pads it to).  The split
+// partials of the row are merged with log-sum-exp weights (exp2 domain), the
+// parts summed in ascending order.  With at most NP parts every partial of
+// the row is loaded in one round (clamped indexes, so the loads are
+// unconditional and all in flight together); longer lists take batches of NP.
+// `lse` as above.
+template <typename T, int HDP, int NP>
 __global__ __launch_bounds__(64) void attention_combine_kernel(const CombineItem *items, const float *part, int Hq,
-                                                               int Hkv, int MT, bf16_t *O, bf16_t *O_lo, int o_perm,
+                                                               int Hkv, int hd, int MT, T *O, T *O_lo, int o_perm,
                                                                float *lse) {
-    static_assert(HD == 128, "a half-wavefront covers one head row");
+    constexpr int LPR = HDP / 4, PART_ROW = HDP + 4;  // lanes per row; floats per partial row
     const CombineItem it = items[blockIdx.x];
     const int t = blockIdx.y;
     const int lane = threadIdx.x;
-    const int i = 2 * blockIdx.z + (lane >> 5);
+    const int i = (64 / LPR) * blockIdx.z + lane / LPR;
     if (i >= it.nrows) return;
     const int G = Hq / Hkv;
     const int rows_item = 16 * MT;
     const int j = it.kvh * G + t;
-    const int d = 4 * (lane & 31);
+    const int d = 4 * (lane % LPR);
     const size_t qstride = (size_t)G * rows_item * PART_ROW;
     const float *base = part + ((size_t)(it.part0 * G + t) * rows_item + i) * PART_ROW;
     const int np = it.nparts;
@@ -414,8 +421,8 @@ __global__ __launch_bounds__(64) void attention_combine_kernel(const CombineItem
 #pragma unroll
         for (int u = 0; u < NP; ++u) {
             const float *p = base + (size_t)min(q0 + u, np - 1) * qstride;
-            mm[u] = p[HD];
-            ll[u] = p[HD + 1];
+            mm[u] = p[HDP];
+            ll[u] = p[HDP + 1];
             oo[u] = *reinterpret_cast<const f32x4 *>(p + d);
         }
         float Mb = M;
@@ -432,20 +439,10 @@ __global__ __launch_bounds__(64) void attention_combine_kernel(const CombineItem
         }
         M = Mb;
     }
-    const int r = it.row0 + i, c = j * HD + d;  // four consecutive columns (adjacent in operand order too)
-    const size_t off = o_perm ? perm_offset(r, c, Hq * HD) : (size_t)r * Hq * HD + c;
-    const f32x4 y = acc / L;
-    uint32_t hi[2], lo[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const bf16_t h0 = f32_to_bf16(y[2 * q]), h1 = f32_to_bf16(y[2 * q + 1]);
-        const bf16_t l0 = f32_to_bf16(y[2 * q] - bf16_to_f32(h0)), l1 = f32_to_bf16(y[2 * q + 1] - bf16_to_f32(h1));
-        hi[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-        lo[q] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-    }
-    *reinterpret_cast<uint2 *>(O + off) = make_uint2(hi[0], hi[1]);
-    *reinterpret_cast<uint2 *>(O_lo + off) = make_uint2(lo[0], lo[1]);
+    const int r = it.row0 + i, c = j * hd + d;
     if (lse && d == 0) lse[(size_t)r * Hq + j] = M + log2f(L);
+    const f32x4 y = acc / L;
+    store_attn4(O, O_lo, r, c, min(4, hd - d), Hq * hd, o_perm, y);
 }
 
 }  // namespace
@@ -455,35 +452,59 @@ int attention_max_row_tiles(int Hq, int Hkv) {
     return G >= 16 ? 1 : std::min(4, std::max(1, 16 / G));
 }
 
-hipError_t launch_attention_mfma(const bf16_t *Q, const bf16_t *Q_lo, const RowInfo *rows,
-                                 const AttnItem *items, int n_items, int MT, int layer, int Hq, int Hkv, float *part,
-                                 bf16_t *O, bf16_t *O_lo, bool o_perm, float *lse, hipStream_t s) {
-    if (n_items <= 0) return hipSuccess;
-    if (!Q_lo || !O_lo || MT < 1 || MT > attention_max_row_tiles(Hq, Hkv)) return hipErrorInvalidValue;
+bool attention_mfma_ok(bool bf16, int Hq, int Hkv, int hd) {
+    return bf16 && (hd == 64 || hd == 128) && Hq / Hkv <= 16;
+}
+
+template <int HD>
+static hipError_t launch_mfma_hd(const bf16_t *Q, const bf16_t *Q_lo, const RowInfo *rows, const AttnItem *items,
+                                 int n_items, int MT, int layer, int Hq, int Hkv, float *part, bf16_t *O, bf16_t *O_lo,
+                                 bool o_perm, float *lse, hipStream_t s) {
     // at most four pairs per item: two key groups of four wavefronts, one pair
     // each; otherwise one group, pairs dealt round-robin to the eight wavefronts
     const int npairs = (Hq / Hkv) * MT;
     if (2 * npairs <= WAVES)
-        kvr_launch(attention_mfma_kernel<1, 2>, dim3(n_items), dim3(64 * WAVES), 0, s, Q, Q_lo, rows, items, layer, Hq,
-                   Hkv, MT, part, O, O_lo, (int)o_perm, lse);
+        kvr_launch((attention_mfma_kernel<HD, 1, 2>), dim3(n_items), dim3(64 * WAVES), 0, s, Q, Q_lo, rows, items, layer,
+                   Hq, Hkv, MT, part, O, O_lo, (int)o_perm, lse);
     else if (npairs <= WAVES)
-        kvr_launch(attention_mfma_kernel<1, 1>, dim3(n_items), dim3(64 * WAVES), 0, s, Q, Q_lo, rows, items, layer, Hq,
-                   Hkv, MT, part, O, O_lo, (int)o_perm, lse);
+        kvr_launch((attention_mfma_kernel<HD, 1, 1>), dim3(n_items), dim3(64 * WAVES), 0, s, Q, Q_lo, rows, items, layer,
+                   Hq, Hkv, MT, part, O, O_lo, (int)o_perm, lse);
     else if (npairs <= 2 * WAVES)
-        kvr_launch(attention_mfma_kernel<2, 1>, dim3(n_items), dim3(64 * WAVES), 0, s, Q, Q_lo, rows, items, layer, Hq,
-                   Hkv, MT, part, O, O_lo, (int)o_perm, lse);
+        kvr_launch((attention_mfma_kernel<HD, 2, 1>), dim3(n_items), dim3(64 * WAVES), 0, s, Q, Q_lo, rows, items, layer,
+                   Hq, Hkv, MT, part, O, O_lo, (int)o_perm, lse);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-hipError_t launch_attention_combine(const CombineItem *items, int n_items, int MT, const float *part, int Hq,
-                                    int Hkv, bf16_t *O, bf16_t *O_lo, bool o_perm, float *lse, hipStream_t s) {
+hipError_t launch_attention_mfma(const bf16_t *Q, const bf16_t *Q_lo, const RowInfo *rows,
+                                 const AttnItem *items, int n_items, int MT, int layer, int Hq, int Hkv, int hd,
+                                 float *part, bf16_t *O, bf16_t *O_lo, bool o_perm, float *lse, hipStream_t s) {
     if (n_items <= 0) return hipSuccess;
-    if (MT < 1 || MT > attention_max_row_tiles(Hq, Hkv)) return hipErrorInvalidValue;
-    kvr_launch(attention_combine_kernel<COMBINE_NP>, dim3(n_items, Hq / Hkv, 8 * MT), dim3(64), 0, s, items, part,
-               Hq, Hkv, MT, O, O_lo, (int)o_perm, lse);
+    if (!Q_lo || !O_lo || MT < 1 || MT > attention_max_row_tiles(Hq, Hkv) || !attention_mfma_ok(true, Hq, Hkv, hd))
+        return hipErrorInvalidValue;
+    return hd == 128 ? launch_mfma_hd<128>(Q, Q_lo, rows, items, n_items, MT, layer, Hq, Hkv, part, O, O_lo, o_perm, lse, s)
+                     : launch_mfma_hd<64>(Q, Q_lo, rows, items, n_items, MT, layer, Hq, Hkv, part, O, O_lo, o_perm, lse, s);
+}
+
+template <typename T>
+static hipError_t launch_combine(const CombineItem *items, int n_items, int MT, const float *part, int Hq, int Hkv,
+                                 int hd, T *O, T *O_lo, bool o_perm, float *lse, hipStream_t s) {
+    if (hd > 64)
+        kvr_launch((attention_combine_kernel<T, 128, COMBINE_NP>), dim3(n_items, Hq / Hkv, 8 * MT), dim3(64), 0, s, items,
+                   part, Hq, Hkv, hd, MT, O, O_lo, (int)o_perm, lse);
+    else
+        kvr_launch((attention_combine_kernel<T, 64, COMBINE_NP>), dim3(n_items, Hq / Hkv, 4 * MT), dim3(64), 0, s, items,
+                   part, Hq, Hkv, hd, MT, O, O_lo, (int)o_perm, lse);
     return hipGetLastError();
+}
+
+hipError_t launch_attention_combine(bool bf16, const CombineItem *items, int n_items, int MT, const float *part, int Hq,
+                                    int Hkv, int hd, void *O, void *O_lo, bool o_perm, float *lse, hipStream_t s) {
+    if (n_items <= 0) return hipSuccess;
+    if (MT < 1 || MT > attention_max_row_tiles(Hq, Hkv) || hd > 128) return hipErrorInvalidValue;
+    if (bf16) return launch_combine(items, n_items, MT, part, Hq, Hkv, hd, (bf16_t *)O, (bf16_t *)O_lo, o_perm, lse, s);
+    return launch_combine(items, n_items, MT, part, Hq, Hkv, hd, (float *)O, (float *)nullptr, o_perm, lse, s);
 }
 
 }  // namespace kvr

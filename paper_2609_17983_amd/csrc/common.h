@@ -208,18 +208,25 @@ hipError_t launch_rope_scatter(bool bf16, const float *qkv, int nsplit, const vo
 // attention launchers also write, when lse is not null, each (row, query head)
 // softmax normaliser as a base-2 log-sum-exp of the scores q.k*log2(e)/sqrt(hd):
 // lse[r * Hq + j].
-hipError_t launch_attention_simple(bool bf16, const void *Q, const void *Q_lo, const RowInfo *rows,
-                                   const DocInfo *docs, int R, int layer, int Hq, int Hkv, int hd, void *O, void *O_lo,
-                                   bool o_perm, float *lse, hipStream_t s);
+// The MFMA kernel takes head_dim 64 and 128 with at most 16 query heads per kv
+// head; the generic kernel the rest (any head_dim up to 128, fp32 or bf16).
+// Both read the same items and write the same partials, whose rows hold
+// attention_part_width(hd) values, the running max and the sum.
+bool attention_mfma_ok(bool bf16, int Hq, int Hkv, int hd);
+constexpr int attention_part_width(int hd) { return hd > 64 ? 128 : 64; }
+constexpr int attention_part_row(int hd) { return attention_part_width(hd) + 4; }
+hipError_t launch_attention_generic(bool bf16, const void *Q, const void *Q_lo, const RowInfo *rows,
+                                    const AttnItem *items, int n_items, int MT, int layer, int Hq, int Hkv, int hd,
+                                    float *part, void *O, void *O_lo, bool o_perm, float *lse, hipStream_t s);
 // Largest number of 16-row tiles an attention work item may carry for a head
 // grouping.  A pass's items all carry at most MT tiles (1 <= MT <= this), the
 // same MT for the MFMA kernel and the combine (it sets the partials' layout).
 int attention_max_row_tiles(int Hq, int Hkv);
 hipError_t launch_attention_mfma(const bf16_t *Q, const bf16_t *Q_lo, const RowInfo *rows,
-                                 const AttnItem *items, int n_items, int MT, int layer, int Hq, int Hkv,
+                                 const AttnItem *items, int n_items, int MT, int layer, int Hq, int Hkv, int hd,
                                  float *part, bf16_t *O, bf16_t *O_lo, bool o_perm, float *lse, hipStream_t s);
-hipError_t launch_attention_combine(const CombineItem *items, int n_items, int MT, const float *part, int Hq,
-                                    int Hkv, bf16_t *O, bf16_t *O_lo, bool o_perm, float *lse, hipStream_t s);
+hipError_t launch_attention_combine(bool bf16, const CombineItem *items, int n_items, int MT, const float *part, int Hq,
+                                    int Hkv, int hd, void *O, void *O_lo, bool o_perm, float *lse, hipStream_t s);
 hipError_t launch_linear_simple(bool bf16, int epi, const LinearArgs &a, hipStream_t s);
 // Skinny MFMA path (R <= 64); nt = 16-row weight tiles per block (1..8).
 hipError_t launch_linear_skinny(int epi, const SkinnyArgs &a, int nt, hipStream_t s);
@@ -287,6 +294,33 @@ hipError_t launch_topk(const float *dev, int m, int K, int p0, int32_t *out, hip
 
 // Attention item geometry shared by the planner and the kernels.
 constexpr int ATT_KT = 64;     // keys per LDS tile
-constexpr int ATT_HD = 128;    // head_dim of the MFMA attention kernel
+
+// Four consecutive output dimensions of an attention row (columns c .. c+n-1,
+// n <= 4 of them real; four together when n == 4 and c is a multiple of 4, where
+// they are adjacent in operand order too), row-major with stride qd or in
+// operand order.
+template <typename T>
+__device__ __forceinline__ void store_attn4(T *O, T *O_lo, int r, int c, int n, int qd, int o_perm, f32x4 y) {
+    if (n < 4 || (c & 3) || (!o_perm && (qd & 3))) {
+        for (int e = 0; e < n; ++e)
+            store_operand(O, O_lo, o_perm ? perm_offset(r, c + e, qd) : (size_t)r * qd + c + e, y[e]);
+        return;
+    }
+    const size_t off = o_perm ? perm_offset(r, c, qd) : (size_t)r * qd + c;
+    if constexpr (sizeof(T) == 4) {
+        *reinterpret_cast<f32x4 *>(O + off) = y;
+    } else {
+        uint32_t hi[2], lo[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const bf16_t h0 = f32_to_bf16(y[2 * q]), h1 = f32_to_bf16(y[2 * q + 1]);
+            const bf16_t l0 = f32_to_bf16(y[2 * q] - bf16_to_f32(h0)), l1 = f32_to_bf16(y[2 * q + 1] - bf16_to_f32(h1));
+            hi[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+            lo[q] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+        }
+        *reinterpret_cast<uint2 *>(O + off) = make_uint2(hi[0], hi[1]);
+        *reinterpret_cast<uint2 *>(O_lo + off) = make_uint2(lo[0], lo[1]);
+    }
+}
 
 }  // namespace kvr

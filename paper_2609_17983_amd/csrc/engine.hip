@@ -128,7 +128,6 @@ namespace {
 
 constexpr int PREFILL_CHUNK = 8192;
 constexpr size_t ATTN_PART_BYTES = 64ull << 20;
-constexpr int PART_ROW = ATT_HD + 4;
 constexpr int SPLIT_MAX = 32;
 
 enum Step {
@@ -230,7 +229,7 @@ void plan_attention(const kvr_ctx *c, Tables &t) {
     long long total_keys = 0;
     for (auto &b : blocks) total_keys += b.kmax;
     int KS = 1 << 30;
-    const size_t slot_floats = (size_t)G * rows_blk * PART_ROW;
+    const size_t slot_floats = (size_t)G * rows_blk * attention_part_row(c->d.head_dim);
     const size_t max_slots = c->attn_part_floats / slot_floats;
     if (split) {
         long long ks = (total_keys * Hkv + target - 1) / target;
@@ -489,10 +488,10 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
     const kvr_dims &d = c->d;
     const int R = (int)t.rows.size();
     if (R == 0) return KVR_OK;
-    const bool attn_mfma = c->bf16 && !c->force_simple && d.head_dim == ATT_HD && d.n_heads / d.n_kv_heads <= 16;
+    const bool attn_mfma = !c->force_simple && attention_mfma_ok(c->bf16, d.n_heads, d.n_kv_heads, d.head_dim);
     const bool sk = skinny_pass_ok(c, R);
     const bool op = c->wpk != nullptr;  // matrix operands in MFMA operand order (both packed-weight kernels)
-    if (attn_mfma) plan_attention(c, t);
+    plan_attention(c, t);
     if ((int)t.items.size() > c->items_cap || (int)t.comb.size() > c->comb_cap)
         return fail(c, KVR_E_RANGE, "attention plan exceeds the context's item capacity");
 
@@ -580,19 +579,19 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
                                       hd, c->rope_cos, c->rope_sin, c->Qb, c->Qb_lo, s), "rope_scatter", ST_ROPE);
         if (l == kv_layer) return KVR_OK;
         float *lse = mh ? mh->lse : nullptr;
-        if (attn_mfma) {
+        if (attn_mfma)
             KVR_CHECK(launch_attention_mfma((const bf16_t *)c->Qb, (const bf16_t *)c->Qb_lo, rows, items,
-                                            (int)t.items.size(), t.att_mt, l, d.n_heads, d.n_kv_heads, c->attn_part,
+                                            (int)t.items.size(), t.att_mt, l, d.n_heads, d.n_kv_heads, hd, c->attn_part,
                                             (bf16_t *)c->Ob, (bf16_t *)c->Ob_lo, op, lse, s),
                       "attention", ST_ATTN);
-            if (!t.comb.empty())
-                KVR_CHECK(launch_attention_combine(comb, (int)t.comb.size(), t.att_mt, c->attn_part, d.n_heads, d.n_kv_heads,
-                                                   (bf16_t *)c->Ob, (bf16_t *)c->Ob_lo, op, lse, s), "attention_combine", ST_COMBINE);
-        } else {
-            KVR_CHECK(launch_attention_simple(bf, c->Qb, c->Qb_lo, rows, docs, R, l, d.n_heads, d.n_kv_heads, hd, c->Ob,
-                                              c->Ob_lo, op, lse, s),
-                      "attention_simple", ST_ATTN);
-        }
+        else
+            KVR_CHECK(launch_attention_generic(bf, c->Qb, c->Qb_lo, rows, items, (int)t.items.size(), t.att_mt, l,
+                                               d.n_heads, d.n_kv_heads, hd, c->attn_part, c->Ob, c->Ob_lo, op, lse, s),
+                      "attention_generic", ST_ATTN);
+        if (!t.comb.empty())
+            KVR_CHECK(launch_attention_combine(bf, comb, (int)t.comb.size(), t.att_mt, c->attn_part, d.n_heads,
+                                               d.n_kv_heads, hd, c->Ob, c->Ob_lo, op, lse, s),
+                      "attention_combine", ST_COMBINE);
         if (mh) {
             KVR_CHECK(launch_attn_mass(bf, c->Qb, c->Qb_lo, mh->lse, R, mh->cache, mh->n_cap, l, d.n_heads,
                                        d.n_kv_heads, hd, mh->n, mh->part, l > 0, s),
@@ -823,7 +822,7 @@ kvr_status kvr_create(const kvr_dims *dims, const kvr_weights *wts, kvr_ctx **ou
     c->max_docs = std::max(1, d.max_rows);
     const int G = d.n_heads / d.n_kv_heads;
     c->attn_part_floats = ATTN_PART_BYTES / 4;
-    const size_t slot_floats = (size_t)G * 16 * PART_ROW;
+    const size_t slot_floats = (size_t)G * 16 * attention_part_row(hd);
     const int max_slots = (int)(c->attn_part_floats / slot_floats);
     const int blocks_cap = c->rows_cap / 16 + c->max_docs + 1;
     c->items_cap = blocks_cap * d.n_kv_heads + max_slots;

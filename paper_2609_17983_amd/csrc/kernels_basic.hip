@@ -1,6 +1,6 @@
 // Row-wise kernels of the decoder pass (embedding gather, RMSNorm, rotary
-// embedding + cache scatter) and the straightforward attention / linear kernels
-// used for fp32 models and for shapes the MFMA kernels do not cover.
+// embedding + cache scatter) and the straightforward linear kernel used for
+// fp32 models and for shapes the MFMA kernels do not cover.
 #include <math.h>
 
 #include "common.h"
@@ -445,47 +445,6 @@ __global__ __launch_bounds__(256) void rope_scatter_vec_kernel(const float *qkv,
     }
 }
 
-// One wavefront per (row, query head): online softmax over keys 0..pos.
-// When `lse` is given, lse[r * Hq + j] = log2 of the softmax normaliser of the
-// scores q.k * log2(e)/sqrt(hd) (the base-2 log-sum-exp).
-template <typename T>
-__global__ __launch_bounds__(64) void attention_simple_kernel(const T *Q, const T *Q_lo, const RowInfo *rows,
-                                                              const DocInfo *docs, int layer, int Hq, int Hkv, int hd,
-                                                              T *O, T *O_lo, int o_perm, float *lse) {
-    const int r = blockIdx.x, j = blockIdx.y, lane = threadIdx.x;
-    const RowInfo ri = rows[r];
-    const DocInfo dc = docs[ri.doc];
-    const int g = j / (Hq / Hkv);
-    const size_t head_stride = (size_t)dc.n_cap * hd;
-    const T *K = (const T *)dc.cache + (((size_t)layer * 2 + 0) * Hkv + g) * head_stride;
-    const T *V = (const T *)dc.cache + (((size_t)layer * 2 + 1) * Hkv + g) * head_stride;
-    const int qd = Hq * hd;
-    const bool has0 = lane < hd, has1 = lane + 64 < hd;
-    const float scale = 1.0f / sqrtf((float)hd);
-    const float q0 = has0 ? load_operand(Q, Q_lo, (size_t)r * qd + j * hd + lane) * scale : 0.f;
-    const float q1 = has1 ? load_operand(Q, Q_lo, (size_t)r * qd + j * hd + lane + 64) * scale : 0.f;
-    float m = -INFINITY, l = 0.f, a0 = 0.f, a1 = 0.f;
-    for (int t = 0; t <= ri.pos; ++t) {
-        const T *kr = K + (size_t)t * hd;
-        float p = (has0 ? q0 * to_f32(kr[lane]) : 0.f) + (has1 ? q1 * to_f32(kr[lane + 64]) : 0.f);
-        p = warp_sum(p);
-        const float mn = fmaxf(m, p);
-        const float corr = expf(m - mn);
-        const float e = expf(p - mn);
-        const T *vr = V + (size_t)t * hd;
-        l = l * corr + e;
-        a0 = a0 * corr + (has0 ? e * to_f32(vr[lane]) : 0.f);
-        a1 = a1 * corr + (has1 ? e * to_f32(vr[lane + 64]) : 0.f);
-        m = mn;
-    }
-    const float inv = 1.0f / l;
-    if (has0) store_operand(O, O_lo, o_perm ? perm_offset(r, j * hd + lane, qd) : (size_t)r * qd + j * hd + lane, a0 * inv);
-    if (has1)
-        store_operand(O, O_lo, o_perm ? perm_offset(r, j * hd + lane + 64, qd) : (size_t)r * qd + j * hd + lane + 64,
-                      a1 * inv);
-    if (lse && lane == 0) lse[(size_t)r * Hq + j] = (m + logf(l)) * 1.4426950408889634f;
-}
-
 __device__ __forceinline__ float silu_f(float z) { return z / (1.0f + expf(-z)); }
 
 // Generic tiled linear layer: 64x64 output tile, 16-wide K steps, 4x4 outputs
@@ -666,21 +625,6 @@ hipError_t launch_rope_scatter(bool bf16, const float *qkv, int nsplit, const vo
         kvr_launch(rope_scatter_kernel<float>, dim3(R), dim3(1024), lds, s, qkv, nsplit, R,
                            (const float *)bq, (const float *)bk, (const float *)bv, rows, docs, layer, Hq, Hkv, hd,
                            rope_cos, rope_sin, (float *)Q, (float *)nullptr);
-    return hipGetLastError();
-}
-
-hipError_t launch_attention_simple(bool bf16, const void *Q, const void *Q_lo, const RowInfo *rows,
-                                   const DocInfo *docs, int R, int layer, int Hq, int Hkv, int hd, void *O, void *O_lo,
-                                   bool o_perm, float *lse, hipStream_t s) {
-    if (R <= 0) return hipSuccess;
-    if (bf16)
-        kvr_launch(attention_simple_kernel<bf16_t>, dim3(R, Hq), dim3(64), 0, s, (const bf16_t *)Q,
-                           (const bf16_t *)Q_lo, rows, docs, layer, Hq, Hkv, hd, (bf16_t *)O, (bf16_t *)O_lo, (int)o_perm, lse);
-    else if (!o_perm)
-        kvr_launch(attention_simple_kernel<float>, dim3(R, Hq), dim3(64), 0, s, (const float *)Q,
-                           (const float *)nullptr, rows, docs, layer, Hq, Hkv, hd, (float *)O, (float *)nullptr, 0, lse);
-    else
-        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -1,0 +1,70 @@
+"""GPU parity of the kernels' shape edges against the fp64 oracle: head widths,
+groupings, ragged matrix sizes and row counts at which a kernel or a branch of
+its dispatch can go wrong.  Same measure and tolerances as the other parity
+tests (1e-5 for fp32, 2e-2 for bf16, relative to the group's largest value)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_17983_amd as kvr
+import synth
+from oracle import decoder as od
+from oracle import select as osel
+from tests.gpu_util import TOL, Engine, OracleWeights, compare_repair, relmax, say, to_device_weights
+
+pytestmark = pytest.mark.gpu
+
+
+def prefill_and_repair(shape, dtype, n, edit, K, policy="edit_local", seed=0):
+    """kvr_prefill of n tokens, then kvr_repair of the oracle's own prefill, both against the oracle."""
+    tdt = torch.bfloat16 if dtype == kvr.KVR_BF16 else torch.float32
+    w = synth.make_weights(shape, dtype=tdt, seed=seed)
+    ow = OracleWeights(w, cache=True)
+    s0, s1 = edit
+    A = osel.select_edit_local(n, s0, s1, K) if policy == "edit_local" else osel.select_random(n, s0, s1, K, seed)
+    P = od.repaired_set(s0, s1, A)
+    eng = Engine(shape, to_device_weights(w), dtype, max_ctx=n + 3, max_rows=max(64, len(P)))
+    try:
+        toks = synth.make_tokens(n, shape.vocab, seed=seed + 1)
+        say(f"case: {shape.name} prefill n={n}")
+        cache = eng.new_cache(n + 3)
+        hidden = torch.empty((n, shape.d_model), device="cuda")
+        eng.prefill(toks.cuda(), cache, hidden)
+        torch.cuda.synchronize()
+        oc, oy = od.prefill(shape, ow, toks.numpy())
+        got = cache.to(torch.float64).cpu().numpy()
+        errs = {(l, kv): relmax(got[l, kv, :, :n], oc[l, kv]) for l in range(shape.n_layers) for kv in range(2)}
+        errs["hidden"] = relmax(hidden.cpu().numpy(), oy)
+        assert max(errs.values()) <= TOL[dtype], errs
+        assert not got[:, :, :, n:].any()  # slots past the context stay as they were
+        say(f"case: {shape.name} repair of {len(P)} rows")
+        new = synth.apply_edit(toks, s0, s1 - s0, shape.vocab)
+        stale = torch.from_numpy(oc).to(tdt).cuda()
+        ref = stale.to(torch.float64).cpu().numpy()
+        after = stale.clone()
+        out = torch.full((len(P), shape.d_model), float("nan"), device="cuda")
+        eng.repair([dict(cache=after, tokens=new.cuda(), edit_start=s0, edit_end=s1, positions=A, hidden=out)])
+        torch.cuda.synchronize()
+        y = od.repair(shape, ow, ref, new.numpy(), s0, s1, A)
+        compare_repair(shape, None, stale, after, out, ref, y, P, n, TOL[dtype], shape.name)
+    finally:
+        eng.close()
+
+
+F32, BF16 = kvr.KVR_F32, kvr.KVR_BF16
+# (dtype, head_dim, query heads, kv heads): the bf16 MFMA kernel takes head_dim 64 (one and two (head, row tile) pairs
+# per wavefront, two key groups) and 128; the generic kernel the rest: widths that are not multiples of four or of 16,
+# both paddings (64 and 128), more than 16 query heads per kv head, one to many pairs per item
+HEADS = [(BF16, 64, 4, 4), (BF16, 64, 8, 2), (BF16, 64, 14, 2), (BF16, 64, 16, 1), (BF16, 64, 17, 1), (BF16, 80, 4, 2),
+         (BF16, 18, 4, 2), (BF16, 128, 18, 1), (F32, 64, 4, 4), (F32, 128, 8, 2), (F32, 6, 6, 2), (F32, 50, 6, 2),
+         (F32, 96, 3, 1), (F32, 20, 33, 1)]
+
+
+@pytest.mark.parametrize("items", ["split", "unsplit"])
+@pytest.mark.parametrize("dtype,hd,hq,hkv", HEADS, ids=[f"{'bf16' if t else 'f32'}-{d}x{a}/{b}" for t, d, a, b in HEADS])
+def test_attention_head_shapes(monkeypatch, dtype, hd, hq, hkv, items):
+    """Short items of two key tiles that a combine merges, and items over all keys of a row block (49 rows and a ragged
+    prefill: the last row tile holds one row)."""
+    monkeypatch.setenv("KVR_ATT_TARGET", "100000" if items == "split" else "1")
+    shape = synth.ModelShape(f"heads {hd}x{hq}/{hkv} {items}", 2, 64, hq, hkv, hd, 64, 128, 1e-5, 10000.0)
+    prefill_and_repair(shape, dtype, 337, (201, 217), 33, seed=hd + hq)
