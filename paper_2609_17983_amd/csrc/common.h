@@ -113,7 +113,7 @@ struct CombineItem {
     int32_t pad[3];
 };
 
-enum Epi { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2 };
+enum Epi { EPI_STORE = 0, EPI_SWIGLU = 2 };
 
 // A linear layer Y[r][n] = sum_k X[r][k] * W[n][k] whose weight is the
 // concatenation of up to three row blocks (Q, K, V), or for SWIGLU the pair
@@ -123,15 +123,14 @@ struct LinearArgs {
     const void *x_lo;     // low part of a compensated bf16 operand, or null
     int32_t ldx;
     int32_t R, K, N;      // N: output columns (SWIGLU: number of features f)
-    const void *w[3];     // row-major row blocks of W (simple kernel)
+    const void *w[3];     // row-major row blocks of W (generic kernel)
     int32_t seg_end[3];   // cumulative output-column boundaries of the blocks
     const void *wp;       // W packed in operand order (tiled kernel; pack.hip)
     int32_t grp;          // tile group of the packed layout (packed_tile_offset)
-    void *out;            // STORE: float [R][ldo]; RESID: float [R][ldo] (+=);
-                          // SWIGLU: operand type [R][ldo]
+    void *out;            // STORE: float [R][ldo]; SWIGLU: operand type [R][ldo]
     void *out_lo;         // SWIGLU: low part of the compensated output, or null
     int32_t ldo;
-    int32_t split;        // tiled STORE only: K cut into `split` slices, partial
+    int32_t split;        // STORE only: K cut into `split` slices, partial
                           // tiles out[s][R][ldo] summed by the consumer (<= 1: none)
     int32_t group_all;    // tiled: at most this many row blocks form one group of the tile order (set by the launcher)
     int32_t tpb;          // tall kernel: weight tiles per block (0: not the tall kernel)
@@ -227,7 +226,10 @@ hipError_t launch_attention_mfma(const bf16_t *Q, const bf16_t *Q_lo, const RowI
                                  float *part, bf16_t *O, bf16_t *O_lo, bool o_perm, float *lse, hipStream_t s);
 hipError_t launch_attention_combine(bool bf16, const CombineItem *items, int n_items, int MT, const float *part, int Hq,
                                     int Hkv, int hd, void *O, void *O_lo, bool o_perm, float *lse, hipStream_t s);
-hipError_t launch_linear_simple(bool bf16, int epi, const LinearArgs &a, hipStream_t s);
+// Any R, N, K, fp32 or bf16, row-major operands (a.w); a.split K slices of a
+// STORE launch go to partial tiles out[s][R][ldo] (generic_split picks them).
+hipError_t launch_linear_generic(bool bf16, int epi, const LinearArgs &a, hipStream_t s);
+int generic_split(int R, int N, int K, size_t part_floats);
 // Skinny MFMA path (R <= 64); nt = 16-row weight tiles per block (1..8).
 hipError_t launch_linear_skinny(int epi, const SkinnyArgs &a, int nt, hipStream_t s);
 // Tiled MFMA path for many rows (packed weight, K a multiple of 32,

@@ -338,12 +338,12 @@ bool pack_ok(const kvr_dims &d, bool force_simple) {
 
 bool skinny_pass_ok(const kvr_ctx *c, int R) { return c->wpk != nullptr && R <= 64; }
 
-// Packed weight: the tiled MFMA kernel, whose activations are in operand
-// order; otherwise the row-major simple kernel.
+// Packed weight: the tall or tiled MFMA kernel, whose activations are in
+// operand order; otherwise the row-major generic kernel.
 hipError_t linear(kvr_ctx *c, int epi, LinearArgs a, hipStream_t s) {
     if (a.wp && a.tpb > 0) return launch_linear_tall(epi, a, s);
     if (a.wp) return launch_linear_tiled(epi, a, s);
-    return launch_linear_simple(c->bf16, epi, a, s);
+    return launch_linear_generic(c->bf16, epi, a, s);
 }
 
 LinearArgs make_args(const void *x, const void *x_lo, int ldx, int R, int K, int N, const void *w0, const void *w1,
@@ -391,19 +391,22 @@ int tiled_split(const kvr_ctx *c, int R, int vrows, int K) {
     return std::max(1, std::min(split, SPLIT_MAX));
 }
 
-// Kernel and K split of a packed-weight projection outside skinny passes: the
-// tall kernel for 64 < R <= 192 rows, the tiled kernel otherwise (split for
-// STORE projections only).  A tall SwiGLU plan with split > 1 runs as a STORE
+// Kernel and K split of a projection outside skinny passes: the generic kernel
+// without packed weights, the tall kernel for 64 < R <= 192 rows, the tiled
+// kernel otherwise (split for STORE projections only).  A tall SwiGLU plan with split > 1 runs as a STORE
 // launch into P followed by the SwiGLU pass (run_pass).  Environment
 // overrides of the tall plan: KVR_TALL=0 (tiled kernel instead),
 // KVR_TALL_TPB (tiles per block), KVR_TALL_SPLIT (STORE split),
 // KVR_TALL_GU_SPLIT (SwiGLU split, 1 or 2), KVR_TALL_STORE_TPB (widest STORE
 // block the planner may take, 12-20).
-void plan_packed(const kvr_ctx *c, LinearArgs &a, int epi) {
+void plan_linear(const kvr_ctx *c, LinearArgs &a, int epi) {
     const int vrows = epi == EPI_SWIGLU ? 2 * a.N : a.N;
     a.tpb = 0;
     a.split = 1;
-    if (!a.wp) return;
+    if (!a.wp) {
+        if (epi == EPI_STORE) a.split = generic_split(a.R, a.N, a.K, c->p_floats);
+        return;
+    }
     if (tall_rows_ok(a.R) && env_int("KVR_TALL", 1) != 0) {
         const bool gu = epi == EPI_SWIGLU;
         const int store_max = std::min(TALL_TPB_WIDE, std::max(TALL_TPB, env_int("KVR_TALL_STORE_TPB", TALL_TPB)));
@@ -554,7 +557,7 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
         if (!sk) {
             qa = make_args(c->Xn, c->Xn_lo, D, R, D, NQKV, w.wq, w.wk, w.wv, qd, qd + kd, pw.qkv, c->P, nullptr, NQKV);
             qa.grp = c->qkv_grp;
-            plan_packed(c, qa, EPI_STORE);
+            plan_linear(c, qa, EPI_STORE);
             rg = tall_row_scale(qa);
         }
         if (rg)
@@ -601,23 +604,20 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
         if (sk) {
             KVR_CHECK(skinny(EPI_STORE, c->Ob, c->Ob_lo, R, qd, D, pw.o, c->o_grp, c->P, nullptr, p_o, s), "o_proj", ST_OPROJ);
             resid_split = p_o.split;
-        } else if (pw.o) {
-            // packed: partial tiles into P (the next RMSNorm adds them to H)
+        } else {
+            // partial tiles into P (the next RMSNorm adds them to H)
             LinearArgs a = make_args(c->Ob, c->Ob_lo, qd, R, qd, D, w.wo, w.wo, w.wo, D, D, pw.o, c->P, nullptr, D);
             a.grp = c->o_grp;
-            plan_packed(c, a, EPI_STORE);
+            plan_linear(c, a, EPI_STORE);
             KVR_CHECK(linear(c, EPI_STORE, a, s), "o_proj", ST_OPROJ);
             resid_split = a.split;
-        } else {
-            KVR_CHECK(linear(c, EPI_RESID, make_args(c->Ob, c->Ob_lo, qd, R, qd, D, w.wo, w.wo, w.wo, D, D, pw.o, c->H, nullptr, D), s),
-                      "o_proj", ST_OPROJ);
         }
         LinearArgs ga{};
         rg = sk;
         if (!sk) {
             ga = make_args(c->Xn, c->Xn_lo, D, R, D, F, w.w_gate, w.w_up, w.w_up, F, F, pw.gu, c->Ab, c->Ab_lo, F);
             ga.grp = c->gu_grp;
-            plan_packed(c, ga, EPI_SWIGLU);
+            plan_linear(c, ga, EPI_SWIGLU);
             rg = tall_row_scale(ga);
         }
         if (rg)
@@ -653,18 +653,12 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
             } else {
                 KVR_CHECK(linear(c, EPI_SWIGLU, ga, s), "gate_up", ST_GATEUP);
             }
-            if (pw.down) {
-                LinearArgs a = make_args(c->Ab, c->Ab_lo, F, R, F, D, w.w_down, w.w_down, w.w_down, D, D, pw.down, c->P,
-                                         nullptr, D);
-                a.grp = c->down_grp;
-                plan_packed(c, a, EPI_STORE);
-                KVR_CHECK(linear(c, EPI_STORE, a, s), "down", ST_DOWN);
-                resid_split = a.split;
-            } else {
-                KVR_CHECK(linear(c, EPI_RESID, make_args(c->Ab, c->Ab_lo, F, R, F, D, w.w_down, w.w_down, w.w_down, D, D,
-                                                         pw.down, c->H, nullptr, D), s),
-                          "down", ST_DOWN);
-            }
+            LinearArgs a = make_args(c->Ab, c->Ab_lo, F, R, F, D, w.w_down, w.w_down, w.w_down, D, D, pw.down, c->P,
+                                     nullptr, D);
+            a.grp = c->down_grp;
+            plan_linear(c, a, EPI_STORE);
+            KVR_CHECK(linear(c, EPI_STORE, a, s), "down", ST_DOWN);
+            resid_split = a.split;
         }
     }
     KVR_CHECK(launch_final_norm(bf, c->H, c->P, resid_split, c->final_norm, rows, docs, R, D, d.rms_eps, s),
@@ -708,12 +702,12 @@ kvr_status score_block(kvr_ctx *c, void *cache, int n, int n_cap, const int32_t 
             nsplit = plan.split;
         } else if (c->bf16) {
             KVR_SCHECK(launch_to_operand(true, false, Y, R, D, c->Xn, c->Xn_lo, s), "lm_head operand", ST_LMHEAD);
-            KVR_SCHECK(launch_linear_simple(true, EPI_STORE, make_args(c->Xn, c->Xn_lo, D, R, D, V, c->lm_head,
+            KVR_SCHECK(launch_linear_generic(true, EPI_STORE, make_args(c->Xn, c->Xn_lo, D, R, D, V, c->lm_head,
                                                                        c->lm_head, c->lm_head, V, V, nullptr,
                                                                        c->score_part, nullptr, V), s),
                        "lm_head", ST_LMHEAD);
         } else {
-            KVR_SCHECK(launch_linear_simple(false, EPI_STORE, make_args(Y, nullptr, D, R, D, V, c->lm_head, c->lm_head,
+            KVR_SCHECK(launch_linear_generic(false, EPI_STORE, make_args(Y, nullptr, D, R, D, V, c->lm_head, c->lm_head,
                                                                         c->lm_head, V, V, nullptr, c->score_part,
                                                                         nullptr, V), s),
                        "lm_head", ST_LMHEAD);
@@ -841,7 +835,8 @@ kvr_status kvr_create(const kvr_dims *dims, const kvr_weights *wts, kvr_ctx **ou
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     // P also takes a split tall gate/up projection's partials (passes of 65-192 rows)
     const size_t tall_rows = c->rows_cap > 64 ? std::min<size_t>(R, 16 * TALL_MT_MAX) : 0;
-    const size_t p_floats = std::max({R * (qd + 2 * kd), (size_t)SPLIT_MAX * 64 * std::max(qd + 2 * kd, D),
+    // (every pass writes the projections' R x D outputs there too)
+    const size_t p_floats = std::max({R * std::max(qd + 2 * kd, D), (size_t)SPLIT_MAX * 64 * std::max(qd + 2 * kd, D),
                                       (size_t)TALL_GU_SPLIT_MAX * tall_rows * 2 * F});
     const size_t lo_es = c->bf16 ? es : 0;  // compensated low parts exist in bf16 only
     const size_t o_H = take(R * D * 4), o_P = take(p_floats * 4), o_Xn = take(R * D * es),

@@ -274,9 +274,7 @@ __global__ __launch_bounds__(64 * TileShape<RT>::NW, TileShape<RT>::BLOCKS_PER_C
             const int r = row0 + lr;
             if (r >= a.R || t >= ntiles) continue;
             const f32x4 v = *reinterpret_cast<const f32x4 *>(&stg[sidx(lr, c)]);
-            f32x4 *o = reinterpret_cast<f32x4 *>(out + (size_t)r * a.ldo + 16 * t + (c & 15));
-            if (EPI == EPI_RESID) *o += v;
-            else *o = v;
+            *reinterpret_cast<f32x4 *>(out + (size_t)r * a.ldo + 16 * t + (c & 15)) = v;
         }
     }
 }
@@ -288,7 +286,6 @@ void launch_rt(int epi, const LinearArgs &a, int tiles, hipStream_t s) {
     dim3 grid((tiles + XCDS - 1) / XCDS * XCDS, epi == EPI_STORE ? std::max(1, (int)a.split) : 1);
     const dim3 block(64 * TileShape<RT>::NW);
     if (epi == EPI_STORE) kvr_launch(linear_tiled_kernel<EPI_STORE, RT>, grid, block, 0, s, a);
-    else if (epi == EPI_RESID) kvr_launch(linear_tiled_kernel<EPI_RESID, RT>, grid, block, 0, s, a);
     else kvr_launch(linear_tiled_kernel<EPI_SWIGLU, RT>, grid, block, 0, s, a);
 }
 

@@ -1,6 +1,5 @@
 // Row-wise kernels of the decoder pass (embedding gather, RMSNorm, rotary
-// embedding + cache scatter) and the straightforward linear kernel used for
-// fp32 models and for shapes the MFMA kernels do not cover.
+// embedding + cache scatter).
 #include <math.h>
 
 #include "common.h"
@@ -445,89 +444,6 @@ __global__ __launch_bounds__(256) void rope_scatter_vec_kernel(const float *qkv,
     }
 }
 
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + expf(-z)); }
-
-// Generic tiled linear layer: 64x64 output tile, 16-wide K steps, 4x4 outputs
-// per thread.  Every index is bounds-checked, so any R, N, K works.
-template <typename T, int EPI>
-__global__ __launch_bounds__(256) void linear_simple_kernel(LinearArgs a) {
-    __shared__ float xs[16][65];
-    __shared__ float ws[16][65];
-    __shared__ float tile[64][65];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int r0 = blockIdx.y * 64;
-    const int c0 = blockIdx.x * 64;
-    const T *X = (const T *)a.x;
-    const T *Xl = (const T *)a.x_lo;
-    // weight row pointer of the tile's column c (0..63); null if out of range
-    auto wrow = [&](int c) -> const T * {
-        if (EPI == EPI_SWIGLU) {
-            const int f = blockIdx.x * 32 + (c & 31);
-            if (f >= a.N) return nullptr;
-            return (const T *)a.w[c >> 5] + (size_t)f * a.K;
-        }
-        const int n = c0 + c;
-        if (n >= a.N) return nullptr;
-        if (n < a.seg_end[0]) return (const T *)a.w[0] + (size_t)n * a.K;
-        if (n < a.seg_end[1]) return (const T *)a.w[1] + (size_t)(n - a.seg_end[0]) * a.K;
-        return (const T *)a.w[2] + (size_t)(n - a.seg_end[1]) * a.K;
-    };
-    float acc[4][4] = {};
-    const int lr = threadIdx.x >> 2;        // 0..63: tile row / column loaded
-    const int lk = (threadIdx.x & 3) * 4;   // 0,4,8,12
-    const T *wr = wrow(lr);
-    const int xr = r0 + lr;
-    for (int k0 = 0; k0 < a.K; k0 += 16) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int k = k0 + lk + e;
-            xs[lk + e][lr] = (xr < a.R && k < a.K) ? load_operand(X, Xl, (size_t)xr * a.ldx + k) : 0.f;
-            ws[lk + e][lr] = (wr && k < a.K) ? to_f32(wr[k]) : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float xv[4], wv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { xv[i] = xs[kk][ty * 4 + i]; wv[i] = ws[kk][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) acc[i][jj] += xv[i] * wv[jj];
-        }
-        __syncthreads();
-    }
-    if (EPI == EPI_SWIGLU) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) tile[ty * 4 + i][tx * 4 + jj] = acc[i][jj];
-        __syncthreads();
-        T *A = (T *)a.out;
-        T *Al = (T *)a.out_lo;
-        for (int idx = threadIdx.x; idx < 64 * 32; idx += 256) {
-            const int rr = idx >> 5, f = idx & 31;
-            const int row = r0 + rr, feat = blockIdx.x * 32 + f;
-            if (row < a.R && feat < a.N)
-                store_operand(A, Al, (size_t)row * a.ldo + feat, silu_f(tile[rr][f]) * tile[rr][32 + f]);
-        }
-        return;
-    }
-    float *out = (float *)a.out;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = r0 + ty * 4 + i;
-        if (row >= a.R) continue;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int n = c0 + tx * 4 + jj;
-            if (n >= a.N) continue;
-            if (EPI == EPI_RESID) out[(size_t)row * a.ldo + n] += acc[i][jj];
-            else out[(size_t)row * a.ldo + n] = acc[i][jj];
-        }
-    }
-}
-
 }  // namespace
 
 hipError_t launch_embed(bool bf16, const RowInfo *rows, const DocInfo *docs, int R, const void *embed, int d,
@@ -625,24 +541,6 @@ hipError_t launch_rope_scatter(bool bf16, const float *qkv, int nsplit, const vo
         kvr_launch(rope_scatter_kernel<float>, dim3(R), dim3(1024), lds, s, qkv, nsplit, R,
                            (const float *)bq, (const float *)bk, (const float *)bv, rows, docs, layer, Hq, Hkv, hd,
                            rope_cos, rope_sin, (float *)Q, (float *)nullptr);
-    return hipGetLastError();
-}
-
-hipError_t launch_linear_simple(bool bf16, int epi, const LinearArgs &a, hipStream_t s) {
-    if (a.R <= 0) return hipSuccess;
-    const int cols_per_block = epi == EPI_SWIGLU ? 32 : 64;
-    dim3 grid((a.N + cols_per_block - 1) / cols_per_block, (a.R + 63) / 64);
-#define KVR_LS(T, E) kvr_launch((linear_simple_kernel<T, E>), grid, dim3(256), 0, s, a)
-    if (bf16) {
-        if (epi == EPI_STORE) KVR_LS(bf16_t, EPI_STORE);
-        else if (epi == EPI_RESID) KVR_LS(bf16_t, EPI_RESID);
-        else KVR_LS(bf16_t, EPI_SWIGLU);
-    } else {
-        if (epi == EPI_STORE) KVR_LS(float, EPI_STORE);
-        else if (epi == EPI_RESID) KVR_LS(float, EPI_RESID);
-        else KVR_LS(float, EPI_SWIGLU);
-    }
-#undef KVR_LS
     return hipGetLastError();
 }
 

@@ -68,3 +68,25 @@ def test_attention_head_shapes(monkeypatch, dtype, hd, hq, hkv, items):
     monkeypatch.setenv("KVR_ATT_TARGET", "100000" if items == "split" else "1")
     shape = synth.ModelShape(f"heads {hd}x{hq}/{hkv} {items}", 2, 64, hq, hkv, hd, 64, 128, 1e-5, 10000.0)
     prefill_and_repair(shape, dtype, 337, (201, 217), 33, seed=hd + hq)
+
+
+# (dtype, d_model, kv heads, ffn, rows of the prefill, repaired rows): the generic projection's tiles (1 to 4 row tiles
+# with K split over the wavefronts; 64 x 64 and 128 x 128 with a last row or column past the edge), K that is not a
+# multiple of 32, of 16, of 4, or is shorter than one step per wavefront, and STORE launches cut into K slices
+LINEARS = [(F32, 12, 1, 10, 65, 3), (F32, 100, 2, 262, 97, 17), (F32, 256, 4, 1003, 129, 48), (BF16, 132, 2, 70, 200, 64),
+           (BF16, 36, 1, 2051, 66, 33), (F32, 1024, 4, 1500, 260, 64), (F32, 2048, 4, 2060, 1030, 65)]
+
+
+@pytest.mark.parametrize("dtype,d,hkv,ffn,n,rows", LINEARS, ids=[f"{'bf16' if c[0] else 'f32'}-d{c[1]}-f{c[3]}-n{c[4]}" for c in LINEARS])
+def test_generic_projection_shapes(dtype, d, hkv, ffn, n, rows):
+    shape = synth.ModelShape(f"generic d{d} f{ffn}", 2 if d < 1000 else 1, d, 2 * hkv, hkv, 6 if d < 200 else 32, ffn, 96,
+                             1e-5, 10000.0)
+    prefill_and_repair(shape, dtype, n, (20, 20 + min(rows, 8)), rows - min(rows, 8), "random", seed=d)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
+def test_wide_residual_long_pass(dtype):
+    """d_model wider than the fused Q|K|V row, and more rows than the partial buffer's fixed part holds: the output and
+    down projections' results fill it up to R x d_model floats."""
+    shape = synth.ModelShape("wide residual", 1, 512, 2, 1, 64, 128, 128, 1e-5, 10000.0)
+    prefill_and_repair(shape, dtype, 2309, (100, 116), 40)
