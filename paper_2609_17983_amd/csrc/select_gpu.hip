@@ -177,16 +177,28 @@ __device__ __forceinline__ uint32_t order_key(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);  // monotone map of floats to unsigned
 }
 
-// Exclusive scan over the block of per-thread counts (thread order).
-__device__ __forceinline__ int block_exclusive_scan(int c, int *buf) {
-    buf[threadIdx.x] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int q = 0; q < 1024; ++q) { const int v = buf[q]; buf[q] = acc; acc += v; }
+constexpr int TOPK_THREADS = 1024, TOPK_WAVES = TOPK_THREADS / 64;
+constexpr int TOPK_LDS_KEYS = 8192;  // keys held in LDS; longer lists are read from memory in every pass
+
+// Exclusive scan of one value per lane over a wavefront (lane order).
+__device__ __forceinline__ int wave_exclusive_scan(int c, int lane) {
+    int v = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(v, o);
+        if (lane >= o) v += u;
     }
+    return v - c;
+}
+
+// Exclusive scan over the block of per-thread counts (thread order).
+__device__ __forceinline__ int block_exclusive_scan(int c, int *totals) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int r = wave_exclusive_scan(c, lane);
+    if (lane == 63) totals[w] = r + c;
     __syncthreads();
-    const int r = buf[threadIdx.x];
+#pragma unroll
+    for (int q = 0; q < TOPK_WAVES; ++q) r += q < w ? totals[q] : 0;
     __syncthreads();
     return r;
 }
@@ -197,50 +209,69 @@ __device__ __forceinline__ int block_exclusive_scan(int c, int *buf) {
 // passes with a 256-bucket histogram); every key above T is taken, and of the
 // keys equal to T the lowest positions fill the rest.  Positions are emitted
 // in ascending order with block scans over contiguous per-thread chunks.
-__global__ __launch_bounds__(1024) void topk_kernel(const float *dev, int m, int K, int p0, int32_t *out) {
-    __shared__ int hist[256];
-    __shared__ int scan[1024];
-    __shared__ uint32_t s_prefix, s_mask;
+//
+// What bounds it: the chain of barriers and LDS round trips of one block.  The
+// keys are read once into LDS, every wavefront counts into a histogram of its
+// own (values share their leading bits, so one histogram's bucket would take
+// every thread's atomic), and the bucket search and the scans run over
+// wavefronts instead of one thread walking 256 and 1024 counts (4000 keys:
+// 42 -> 13.6 us).
+__global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const float *dev, int m, int K, int p0, int32_t *out) {
+    __shared__ uint32_t keys[TOPK_LDS_KEYS];
+    __shared__ int hist[TOPK_WAVES][256];
+    __shared__ int totals[TOPK_WAVES];
+    __shared__ uint32_t s_prefix;
     __shared__ int s_left;
-    if (threadIdx.x == 0) { s_prefix = 0; s_mask = 0; s_left = K; }
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const bool held = m <= TOPK_LDS_KEYS;
+    if (held)
+        for (int i = tid; i < m; i += TOPK_THREADS) keys[i] = order_key(dev[i]);
+    auto key = [&](int i) { return held ? keys[i] : order_key(dev[i]); };
+    uint32_t prefix = 0, mask = 0;
+    int left = K;  // keys still needed among those that match the prefix
     for (int shift = 24; shift >= 0; shift -= 8) {
-        for (int i = threadIdx.x; i < 256; i += 1024) hist[i] = 0;
+        for (int i = tid; i < TOPK_WAVES * 256; i += TOPK_THREADS) hist[i >> 8][i & 255] = 0;
         __syncthreads();
-        const uint32_t prefix = s_prefix, mask = s_mask;
-        for (int i = threadIdx.x; i < m; i += 1024) {
-            const uint32_t k = order_key(dev[i]);
-            if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255], 1);
+        for (int i = tid; i < m; i += TOPK_THREADS) {
+            const uint32_t k = key(i);
+            if ((k & mask) == prefix) atomicAdd(&hist[w][(k >> shift) & 255], 1);
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int left = s_left, b = 255;
-            for (; b > 0 && hist[b] < left; --b) left -= hist[b];
-            s_left = left;  // keys still needed from bucket b
-            s_prefix = prefix | ((uint32_t)b << shift);
-            s_mask = mask | (255u << shift);
+        // the bucket holding the left-th largest: thread t < 256 counts bucket
+        // 255 - t, so that an exclusive scan is the number of larger keys
+        int c = 0;
+        if (tid < 256)
+#pragma unroll
+            for (int q = 0; q < TOPK_WAVES; ++q) c += hist[q][255 - tid];
+        const int above = block_exclusive_scan(c, totals);
+        if (tid < 256 && above < left && left <= above + c) {
+            s_prefix = prefix | ((uint32_t)(255 - tid) << shift);
+            s_left = left - above;
         }
         __syncthreads();
+        prefix = s_prefix;
+        left = s_left;
+        mask |= 255u << shift;
     }
-    const uint32_t T = s_prefix;
-    const int ties = s_left;  // keys equal to T to take, lowest positions first
-    const int chunk = (m + 1023) / 1024;
-    const int b0 = min(m, threadIdx.x * chunk), b1 = min(m, b0 + chunk);
+    const uint32_t T = prefix;
+    const int ties = left;  // keys equal to T to take, lowest positions first
+    const int chunk = (m + TOPK_THREADS - 1) / TOPK_THREADS;
+    const int b0 = min(m, tid * chunk), b1 = min(m, b0 + chunk);
     int eq = 0;
-    for (int i = b0; i < b1; ++i) eq += order_key(dev[i]) == T;
-    int eq_before = block_exclusive_scan(eq, scan);
+    for (int i = b0; i < b1; ++i) eq += key(i) == T;
+    const int eq_before = block_exclusive_scan(eq, totals);
     int sel = 0;
     {
         int e = eq_before;
         for (int i = b0; i < b1; ++i) {
-            const uint32_t k = order_key(dev[i]);
+            const uint32_t k = key(i);
             sel += k > T || (k == T && e++ < ties);
         }
     }
-    int o = block_exclusive_scan(sel, scan);
+    int o = block_exclusive_scan(sel, totals);
     int e = eq_before;
     for (int i = b0; i < b1; ++i) {
-        const uint32_t k = order_key(dev[i]);
+        const uint32_t k = key(i);
         if (k > T || (k == T && e++ < ties)) out[o++] = p0 + i;
     }
 }

@@ -90,3 +90,29 @@ def test_wide_residual_long_pass(dtype):
     down projections' results fill it up to R x d_model floats."""
     shape = synth.ModelShape("wide residual", 1, 512, 2, 1, 64, 128, 128, 1e-5, 10000.0)
     prefill_and_repair(shape, dtype, 2309, (100, 116), 40)
+
+
+@pytest.mark.parametrize("n", [40, 1300, 9001], ids=lambda n: f"n{n}")
+def test_topk_sizes(n):
+    """The selection follows from the deviations the call returns: fewer keys than threads, and more than the block
+    holds in LDS; one key, ties in bulk (duplicated cache rows) and the whole pool."""
+    shape = synth.ModelShape("topk", 1, 16, 2, 1, 8, 16, 64, 1e-5, 10000.0)
+    w = synth.make_weights(shape, dtype=torch.float32, seed=5)
+    eng = Engine(shape, to_device_weights(w), F32, max_ctx=n, max_rows=64)
+    try:
+        toks = torch.full((n,), 3, dtype=torch.int32, device="cuda")  # equal values: V deviates alike at layer 0
+        cache = torch.randn((1, 2, 1, n, 8), device="cuda")
+        cache[:, :, :, : n // 2] = 0
+        m = n - 1 - 5
+        for K in (1, 7, m // 2, m):
+            sel = torch.full((K,), -1, dtype=torch.int32, device="cuda")
+            dev = torch.empty(m, device="cuda")
+            say(f"case: top-{K} of {m}")
+            got = kvr.kvr_select_cacheblend(eng.ctx, cache.data_ptr(), n, n, toks.data_ptr(), 2, 5, K, 0, sel.data_ptr(),
+                                            dev.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            d = dev.cpu().numpy()
+            want = np.sort(np.lexsort((np.arange(m), -d))[:K]) + 5
+            assert got == K and np.array_equal(sel.cpu().numpy(), want)
+    finally:
+        eng.close()
