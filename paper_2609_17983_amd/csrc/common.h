@@ -294,6 +294,20 @@ hipError_t launch_mass_reduce(const float *part, int Hkv, int n, float *mass, hi
 // The K largest of dev[0, m) (ties: lower index), as ascending positions p0 + i.
 hipError_t launch_topk(const float *dev, int m, int K, int p0, int32_t *out, hipStream_t s);
 
+// Transplant: cache rows [start, start + len) of each segment, copied in every
+// plane.  The list travels as a kernel argument (HIP's limit is 4 KB), so a
+// call needs no staging buffer and can be captured.
+constexpr int COPY_SEGMENTS = 720, COPY_LEN = 16, COPY_PLANES = 4;
+struct CopySegments {
+    int32_t n;
+    int32_t start[COPY_SEGMENTS];
+    uint8_t len[COPY_SEGMENTS];  // 1 .. COPY_LEN
+};
+// row: bytes of a cache row (a multiple of 4; caches are 16-byte aligned); the
+// plane strides are in bytes.
+hipError_t launch_copy_rows(const CopySegments &sg, const void *src, size_t src_plane, void *dst, size_t dst_plane,
+                            int row, int planes, hipStream_t s);
+
 // Attention item geometry shared by the planner and the kernels.
 constexpr int ATT_KT = 64;     // keys per LDS tile
 

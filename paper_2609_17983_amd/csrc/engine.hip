@@ -1009,17 +1009,24 @@ kvr_status kvr_transplant(kvr_ctx *c, const void *d_src, int32_t src_n_cap, void
     DeviceGuard g(c->device);
     hipStream_t s = (hipStream_t)stream;
     const size_t row = (size_t)c->d.head_dim * elem_size(c->d);
-    const size_t planes = (size_t)c->d.n_layers * 2 * c->d.n_kv_heads;
+    const int planes = c->d.n_layers * 2 * c->d.n_kv_heads;
+    // one launch per COPY_SEGMENTS runs of consecutive positions (a 2-D copy
+    // per run took 2.4 us each: 463 runs in 32 layers, 1297 -> 40 us a call,
+    // 138 MB read and written at 4.5 TB/s)
+    CopySegments sg;
+    sg.n = 0;
     for (int i = 0; i < n_positions;) {
         int j = i + 1;
-        while (j < n_positions && h_positions[j] == h_positions[j - 1] + 1) ++j;
-        const size_t p0 = (size_t)h_positions[i];
-        // one 2-D copy: `planes` rows of (j - i) cache rows each
-        hipError_t e = hipMemcpy2DAsync((char *)d_dst + p0 * row, (size_t)dst_n_cap * row,
-                                        (const char *)d_src + p0 * row, (size_t)src_n_cap * row, (size_t)(j - i) * row,
-                                        planes, hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return hip_fail(c, e, "kvr_transplant: hipMemcpy2DAsync");
+        while (j < n_positions && j - i < COPY_LEN && h_positions[j] == h_positions[j - 1] + 1) ++j;
+        sg.start[sg.n] = h_positions[i];
+        sg.len[sg.n++] = (uint8_t)(j - i);
         i = j;
+        if (sg.n == COPY_SEGMENTS || i == n_positions) {
+            const hipError_t e = launch_copy_rows(sg, d_src, (size_t)src_n_cap * row, d_dst, (size_t)dst_n_cap * row,
+                                                  (int)row, planes, s);
+            if (e != hipSuccess) return hip_fail(c, e, "kvr_transplant: copy");
+            sg.n = 0;
+        }
     }
     return KVR_OK;
 }

@@ -1,7 +1,7 @@
 // Device side of the forward-based selectors of Table 1: the CacheBlend
 // per-position deviation between freshly computed and stale keys/values, the
-// Attention selector's per-position attention mass from the query rows, and a
-// block-wide top-K.
+// Attention selector's per-position attention mass from the query rows, a
+// block-wide top-K, and transplant's row copy.
 #include <math.h>
 
 #include "common.h"
@@ -276,6 +276,29 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const float *dev, in
     }
 }
 
+// Transplant: copies the rows of a segment list, every plane (layer, key or
+// value, kv head), from one cache to another.  16 lanes take a segment row,
+// four planes at a time so that four loads are in flight per lane.
+template <typename V>
+__global__ __launch_bounds__(256) void copy_rows_kernel(CopySegments sg, const char *src, size_t src_plane, char *dst,
+                                                        size_t dst_plane, int row, int planes) {
+    constexpr int P = COPY_PLANES;
+    const int q = blockIdx.y * 16 + (threadIdx.x >> 4), pl = blockIdx.x * P;
+    if (q >= sg.n) return;
+    const size_t p0 = (size_t)sg.start[q] * row;
+    const int bytes = sg.len[q] * row;
+    const int np = min(P, planes - pl);
+    for (int b = (threadIdx.x & 15) * (int)sizeof(V); b < bytes; b += 16 * (int)sizeof(V)) {
+        V v[P];
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+            v[u] = *reinterpret_cast<const V *>(src + (size_t)(pl + min(u, np - 1)) * src_plane + p0 + b);
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+            if (u < np) *reinterpret_cast<V *>(dst + (size_t)(pl + u) * dst_plane + p0 + b) = v[u];
+    }
+}
+
 }  // namespace
 
 hipError_t launch_kv_deviation(bool bf16, const void *fresh, int fresh_ncap, int fl, const void *stale, int stale_ncap,
@@ -323,6 +346,20 @@ hipError_t launch_topk(const float *dev, int m, int K, int p0, int32_t *out, hip
     if (K <= 0 || m <= 0) return hipSuccess;
     if (K > m) return hipErrorInvalidValue;
     kvr_launch(topk_kernel, dim3(1), dim3(1024), 0, s, dev, m, K, p0, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_rows(const CopySegments &sg, const void *src, size_t src_plane, void *dst, size_t dst_plane,
+                            int row, int planes, hipStream_t s) {
+    if (sg.n <= 0 || planes <= 0) return hipSuccess;
+    if (row % 4 != 0) return hipErrorInvalidValue;
+    const dim3 grid((planes + COPY_PLANES - 1) / COPY_PLANES, (sg.n + 15) / 16);
+    if (row % 16 == 0)
+        kvr_launch(copy_rows_kernel<u32x4>, grid, dim3(256), 0, s, sg, (const char *)src, src_plane, (char *)dst, dst_plane,
+                   row, planes);
+    else
+        kvr_launch(copy_rows_kernel<uint32_t>, grid, dim3(256), 0, s, sg, (const char *)src, src_plane, (char *)dst,
+                   dst_plane, row, planes);
     return hipGetLastError();
 }
 

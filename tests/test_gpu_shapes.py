@@ -116,3 +116,28 @@ def test_topk_sizes(n):
             assert got == K and np.array_equal(sel.cpu().numpy(), want)
     finally:
         eng.close()
+
+
+# (dtype, layers, kv heads, head_dim): cache rows of 16-byte units and of 4-byte ones, planes that fill no group of four
+@pytest.mark.parametrize("dtype,L,hkv,hd", [(F32, 1, 1, 6), (BF16, 3, 3, 18), (F32, 2, 1, 64), (BF16, 5, 1, 128)],
+                         ids=["f32-6", "bf16-18", "f32-64", "bf16-128"])
+def test_transplant_segments(dtype, L, hkv, hd):
+    """Runs longer than a segment, single positions, and more segments than one launch carries."""
+    shape = synth.ModelShape("copy", L, 4 if hd < 64 else 64, 2 * hkv, hkv, hd, 64, 64, 1e-5, 10000.0)
+    w = synth.make_weights(shape, dtype=torch.float32 if dtype == F32 else torch.bfloat16)
+    eng = Engine(shape, to_device_weights(w), dtype, max_ctx=3000, max_rows=1)
+    try:
+        rng = np.random.default_rng(hd)
+        src = torch.randn((L, 2, hkv, 2900, hd), device="cuda").to(eng.tdtype)
+        for pos in ([0], list(range(7, 7 + 33)), sorted(rng.choice(2800, size=1700, replace=False).tolist()),
+                    list(range(0, 2800, 2)), list(range(2800))):
+            dst = torch.randn((L, 2, hkv, 2800, hd), device="cuda").to(eng.tdtype)
+            ref = dst.clone()
+            ref[:, :, :, pos] = src[:, :, :, pos]
+            say(f"case: transplant of {len(pos)} positions")
+            kvr.kvr_transplant(eng.ctx, src.data_ptr(), 2900, dst.data_ptr(), 2800, pos,
+                               torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert torch.equal(dst, ref)
+    finally:
+        eng.close()
