@@ -133,6 +133,7 @@ struct LinearArgs {
     int32_t split;        // STORE only: K cut into `split` slices, partial
                           // tiles out[s][R][ldo] summed by the consumer (<= 1: none)
     int32_t group_all;    // tiled: at most this many row blocks form one group of the tile order (set by the launcher)
+    int32_t rt;           // tiled kernel: 16-row tiles per block
     int32_t tpb;          // tall kernel: weight tiles per block (0: not the tall kernel)
     // tall kernel: RMS scale of the rows (resid_gain), as in SkinnyArgs: when
     // rs_ssq is set, output row r is multiplied by
@@ -233,7 +234,7 @@ int generic_split(int R, int N, int K, size_t part_floats);
 // Skinny MFMA path (R <= 64); nt = 16-row weight tiles per block (1..8).
 hipError_t launch_linear_skinny(int epi, const SkinnyArgs &a, int nt, hipStream_t s);
 // Tiled MFMA path for many rows (packed weight, K a multiple of 32,
-// activations in operand order).
+// activations in operand order); a.rt and a.split come from plan_tiled.
 hipError_t launch_linear_tiled(int epi, const LinearArgs &a, hipStream_t s);
 // Tall MFMA path for 64 < R <= 16 * TALL_MT_MAX rows (packed weight,
 // activations in operand order): a block holds every row; a.tpb weight tiles
@@ -256,9 +257,10 @@ hipError_t launch_linear_tall(int epi, const LinearArgs &a, hipStream_t s);
 // feature 8t + j for j < 8, up of feature 8t + j - 8 otherwise); A is written
 // as a compensated pair in operand order ([R][F], F a multiple of 32).
 hipError_t launch_swiglu_partials(const float *part, int nsplit, int R, int F, bf16_t *A, bf16_t *A_lo, hipStream_t s);
-// Output-tile blocks the tiled kernel launches for R rows and vrows weight
-// rows (before any K split), and how many of them the chip runs at once.
-int tiled_blocks(int R, int vrows, int *slots);
+// Tiled kernel: row tiles per block (a.rt) and K slices (a.split) for R rows
+// and vrows weight rows; partial tiles stay within p_floats.
+struct TiledPlan { int rt, split; };
+TiledPlan plan_tiled(int R, int vrows, int K, bool split_ok, size_t p_floats);
 // Repack up to three row-major bf16 matrices (rows [0,e0), [e0,e1), [e1,V) of
 // the virtual matrix; interleave: w0 = gate, w1 = up, tile t = gate rows
 // 8t..8t+7 then up rows 8t..8t+7) of K columns into operand order at dst.

@@ -378,19 +378,6 @@ hipError_t skinny(int epi, const void *x, const void *x_lo, int R, int K, int N,
     return launch_linear_skinny(epi, a, p.nt, s);
 }
 
-// K slices for a tiled projection of R rows into vrows outputs whose partial
-// tiles go to P: enough blocks for about two per compute unit, at least 16
-// k-steps per slice, and no more partial tiles than P holds (1: no split).
-int tiled_split(const kvr_ctx *c, int R, int vrows, int K) {
-    int slots = 0;
-    const int blocks = tiled_blocks(R, vrows, &slots);
-    if (blocks >= 2 * 256) return 1;
-    int split = (2 * 256 + blocks - 1) / blocks;
-    split = std::min(split, std::max(1, K / 32 / 16));
-    split = std::min<long long>(split, (long long)(c->p_floats / ((size_t)R * vrows)));
-    return std::max(1, std::min(split, SPLIT_MAX));
-}
-
 // Kernel and K split of a projection outside skinny passes: the generic kernel
 // without packed weights, the tall kernel for 64 < R <= 192 rows, the tiled
 // kernel otherwise (split for STORE projections only).  A tall SwiGLU plan with split > 1 runs as a STORE
@@ -424,7 +411,9 @@ void plan_linear(const kvr_ctx *c, LinearArgs &a, int epi) {
         a.split = p.split;
         return;
     }
-    if (epi == EPI_STORE) a.split = tiled_split(c, a.R, vrows, a.K);
+    const TiledPlan p = plan_tiled(a.R, vrows, a.K, epi == EPI_STORE, c->p_floats);
+    a.rt = p.rt;
+    a.split = p.split;
 }
 
 // A tall projection reading the RMSNorm output applies the RMS scale to its

@@ -141,3 +141,15 @@ def test_transplant_segments(dtype, L, hkv, hd):
             assert torch.equal(dst, ref)
     finally:
         eng.close()
+
+
+# 448 x 3136: an odd number of k-steps per row (14, 98), a gate/up matrix of 24.5 column blocks, bias, seven heads per group
+TILED = synth.ModelShape("tiled", 2, 448, 14, 2, 128, 3136, 256, 1e-6, 1e6, qkv_bias=True)
+
+
+@pytest.mark.parametrize("rt", ["", "4", "5", "6", "7", "8"], ids=lambda r: r or "planned")
+def test_tiled_row_tiles(monkeypatch, rt):
+    """Each of the tiled kernel's block heights (the last row block holds one to seven row tiles, the last row tile one
+    row) and the planned one; the repair's projections are cut into K slices of unequal length."""
+    monkeypatch.setenv("KVR_TILED_RT", rt)
+    prefill_and_repair(TILED, BF16, 785, (301, 317), 234, "random", seed=2)
