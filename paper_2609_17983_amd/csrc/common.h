@@ -183,14 +183,30 @@ inline void kvr_launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, uint32_t
 
 // ---- launchers (each enqueues one kernel on `stream`; return hipSuccess or the launch error)
 
-hipError_t launch_embed(bool bf16, const RowInfo *rows, const DocInfo *docs, int R, const void *embed,
-                        int d, int vocab, float *H, hipStream_t s);
+// First kernel of a pass: H = the rows' embeddings and, with `gain`, layer 0's
+// X = H * gain and sums of squares (resid_gain).  The rows come from `pos` and
+// `tokens` (one document, R <= EMBED_ROWS) or, with tokens null, from the row
+// and document tables (host or device memory).  upload_16 > 0: the kernel also
+// copies that many 16-byte units from pinned host memory to upload_dst.
+constexpr int EMBED_ROWS = 256;
+struct EmbedArgs {
+    const RowInfo *rows;
+    const DocInfo *docs;
+    const int32_t *tokens;
+    const u32x4 *upload_src;
+    u32x4 *upload_dst;
+    int32_t upload_16;
+    int32_t R, row_blocks;  // row_blocks: set by the launcher
+    int32_t pos[EMBED_ROWS];
+};
+hipError_t launch_embed(bool bf16, const EmbedArgs &args, const void *embed, const void *gain, int d, int vocab, float *H,
+                        void *X, void *X_lo, float *ssq, hipStream_t s);
 // RMSNorm of the residual rows.  First H[r] += sum of `nsplit` fp32 partial
 // tiles part[s][R][d] (the split-K outputs of the projection that produced the
 // residual update; nsplit 0 = none), then X = H * rsqrt(mean(H^2)+eps) * gain,
 // row-major with stride ldx, or in operand order when `perm`.
-hipError_t launch_rmsnorm(bool bf16_out, bool bf16_gain, float *H, const float *part, int nsplit, const void *gain,
-                          int R, int d, float eps, void *X, void *X_lo, int ldx, bool perm, hipStream_t s);
+hipError_t launch_rmsnorm(bool bf16, float *H, const float *part, int nsplit, const void *gain, int R, int d, float eps,
+                          void *X, void *X_lo, int ldx, bool perm, hipStream_t s);
 // Residual update + gain for the skinny path (see resid_gain_kernel): H[r] +=
 // partials, X = H * gain (compensated, operand order), ssq[b][r] per 1024-column
 // block b; resid_gain_blocks(d) blocks per row.
@@ -267,9 +283,6 @@ TiledPlan plan_tiled(int R, int vrows, int K, bool split_ok, size_t p_floats);
 hipError_t launch_pack_weight(const void *w0, const void *w1, const void *w2, int e0, int e1, bool interleave,
                               int V, int K, int grp, void *dst, hipStream_t s);
 
-// Scoring rows: hidden rows Y [R][d] fp32 -> LM-head operand (compensated
-// bf16 pair, operand order or row-major, or fp32 row-major).
-hipError_t launch_to_operand(bool bf16, bool perm, const float *Y, int R, int d, void *X, void *X_lo, hipStream_t s);
 // Log-softmax of R rows of V logits (sum of nsplit fp32 tiles part[s][R][V]):
 // lp[r] = log p(target[r]) for r < n_targets, argmax[r] (lowest index among
 // maxima; argmax may be null), next[0] = argmax of row R-1 when next is given.

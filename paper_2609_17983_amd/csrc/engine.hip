@@ -83,7 +83,6 @@ struct kvr_ctx {
     size_t lm_pk_bytes = 0;
     char *sel_scratch = nullptr;  // selectors: CacheBlend fresh keys/values + deviations; Attention mass
     size_t sel_bytes = 0;
-    float *score_y = nullptr;     // hidden rows of the scored block [max rows][d]
     float *score_part = nullptr;  // logit tiles [split][64][vocab]
     void *score_lsm = nullptr;    // log-softmax chunk statistics
     size_t score_bytes = 0;
@@ -129,6 +128,7 @@ namespace {
 constexpr int PREFILL_CHUNK = 8192;
 constexpr size_t ATTN_PART_BYTES = 64ull << 20;
 constexpr int SPLIT_MAX = 32;
+constexpr size_t UPLOAD_BY_KERNEL = 64 << 10;  // bytes of tables the pass's first kernel uploads
 
 enum Step {
     ST_EMBED, ST_NORM, ST_QKV, ST_ROPE, ST_ATTN, ST_COMBINE, ST_OPROJ, ST_GATEUP, ST_DOWN, ST_FINAL, ST_LMHEAD,
@@ -475,8 +475,11 @@ struct MassHook {
 
 // Upload the tables of a pass and enqueue its kernels.  kv_layer >= 0 stops
 // the pass at that layer once its fresh keys/values are in the cache (layers
-// below it run in full; no final norm).
-kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, const MassHook *mh = nullptr) {
+// below it run in full; no final norm).  lm_operand: the final norm's rows go
+// to Xn as the LM head's operand (packed head: operand order) instead of to
+// the documents' hidden rows.
+kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, const MassHook *mh = nullptr,
+                    bool lm_operand = false) {
     const kvr_dims &d = c->d;
     const int R = (int)t.rows.size();
     if (R == 0) return KVR_OK;
@@ -502,11 +505,13 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
     memcpy(c->h_stage + o_docs, t.docs.data(), t.docs.size() * sizeof(DocInfo));
     if (!t.items.empty()) memcpy(c->h_stage + o_items, t.items.data(), t.items.size() * sizeof(AttnItem));
     if (!t.comb.empty()) memcpy(c->h_stage + o_comb, t.comb.data(), t.comb.size() * sizeof(CombineItem));
-    hipError_t e = hipMemcpyAsync(c->d_tables, c->h_stage, total, hipMemcpyHostToDevice, s);
+    // Small tables are uploaded by the pass's first kernel, larger ones by a
+    // copy in front of it (a kernel's reads of host memory are slower than the
+    // copy engine's once latency no longer dominates).
+    const bool by_kernel = total <= UPLOAD_BY_KERNEL;
+    hipError_t e = hipSuccess;
+    if (!by_kernel) e = hipMemcpyAsync(c->d_tables, c->h_stage, total, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync(tables)");
-    e = hipEventRecord(c->stage_ev, s);
-    if (e != hipSuccess) return hip_fail(c, e, "hipEventRecord(staging)");
-    c->stage_pending = true;
     const RowInfo *rows = (const RowInfo *)c->d_tables;
     const DocInfo *docs = (const DocInfo *)(c->d_tables + o_docs);
     const AttnItem *items = (const AttnItem *)(c->d_tables + o_items);
@@ -533,7 +538,34 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
         if (err_ != hipSuccess) return hip_fail(c, err_, what);                    \
     } while (0)
 
-    KVR_CHECK(launch_embed(bf, rows, docs, R, c->embed, D, d.vocab, c->H, s), "embed", ST_EMBED);
+    EmbedArgs ea;
+    ea.R = R;
+    const char *tab = by_kernel ? c->h_stage : c->d_tables;
+    ea.rows = (const RowInfo *)tab;
+    ea.docs = (const DocInfo *)(tab + o_docs);
+    ea.tokens = nullptr;
+    if (t.docs.size() == 1 && R <= EMBED_ROWS) {
+        ea.tokens = t.docs[0].tokens;
+        for (int i = 0; i < R; ++i) ea.pos[i] = t.rows[i].pos;
+    }
+    ea.upload_src = (const u32x4 *)c->h_stage;
+    ea.upload_dst = (u32x4 *)c->d_tables;
+    ea.upload_16 = by_kernel ? (int32_t)((total + 15) / 16) : 0;
+    // layer 0 of a pass whose projections apply the RMS scale: the embedding
+    // kernel makes the first operand too
+    bool first_gain = sk;
+    if (!sk) {
+        LinearArgs q0 = make_args(c->Xn, c->Xn_lo, D, R, D, NQKV, nullptr, nullptr, nullptr, qd, qd + kd,
+                                  c->wpk ? c->pk[0].qkv : nullptr, c->P, nullptr, NQKV);
+        plan_linear(c, q0, EPI_STORE);
+        first_gain = tall_row_scale(q0);
+    }
+    KVR_CHECK(launch_embed(bf, ea, c->embed, first_gain ? c->layers[0].attn_norm : nullptr, D, d.vocab, c->H, c->Xn,
+                           c->Xn_lo, c->rs_ssq, s), "embed", ST_EMBED);
+    // the staging buffer is free once the copy or the first kernel is through
+    e = hipEventRecord(c->stage_ev, s);
+    if (e != hipSuccess) return hip_fail(c, e, "hipEventRecord(staging)");
+    c->stage_pending = true;
     int resid_split = 0;  // partial tiles in P still to be added to H
     const int n_run = kv_layer >= 0 ? kv_layer + 1 : d.n_layers;
     for (int l = 0; l < n_run; ++l) {
@@ -549,11 +581,13 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
             plan_linear(c, qa, EPI_STORE);
             rg = tall_row_scale(qa);
         }
-        if (rg)
+        if (rg && l == 0) {
+            // the embedding kernel's
+        } else if (rg)
             KVR_CHECK(launch_resid_gain(bf, c->H, c->P, resid_split, w.attn_norm, R, D, c->Xn, c->Xn_lo, c->rs_ssq, s),
                       "rmsnorm(attn)", ST_NORM);
         else
-            KVR_CHECK(launch_rmsnorm(bf, bf, c->H, c->P, resid_split, w.attn_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo, D,
+            KVR_CHECK(launch_rmsnorm(bf, c->H, c->P, resid_split, w.attn_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo, D,
                                      op, s),
                       "rmsnorm(attn)", ST_NORM);
         int qkv_split = 1;
@@ -613,7 +647,7 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
             KVR_CHECK(launch_resid_gain(bf, c->H, c->P, resid_split, w.mlp_norm, R, D, c->Xn, c->Xn_lo, c->rs_ssq, s),
                       "rmsnorm(mlp)", ST_NORM);
         else
-            KVR_CHECK(launch_rmsnorm(bf, bf, c->H, c->P, resid_split, w.mlp_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo, D, op,
+            KVR_CHECK(launch_rmsnorm(bf, c->H, c->P, resid_split, w.mlp_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo, D, op,
                                      s),
                       "rmsnorm(mlp)", ST_NORM);
         resid_split = 0;
@@ -650,8 +684,12 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
             resid_split = a.split;
         }
     }
-    KVR_CHECK(launch_final_norm(bf, c->H, c->P, resid_split, c->final_norm, rows, docs, R, D, d.rms_eps, s),
-              "final_norm", ST_FINAL);
+    if (lm_operand)
+        KVR_CHECK(launch_rmsnorm(bf, c->H, c->P, resid_split, c->final_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo, D,
+                                 c->lm_pk != nullptr, s), "final_norm", ST_FINAL);
+    else
+        KVR_CHECK(launch_final_norm(bf, c->H, c->P, resid_split, c->final_norm, rows, docs, R, D, d.rms_eps, s),
+                  "final_norm", ST_FINAL);
 #undef KVR_CHECK
     return KVR_OK;
 }
@@ -666,10 +704,10 @@ kvr_status score_block(kvr_ctx *c, void *cache, int n, int n_cap, const int32_t 
     const int D = d.d_model, V = d.vocab;
     Tables &t = c->tab;
     t.clear();
-    t.docs.push_back(DocInfo{cache, tokens, c->score_y, n + m, n_cap, 0, m});
+    t.docs.push_back(DocInfo{cache, tokens, nullptr, n + m, n_cap, 0, m});
     t.rows.reserve(m);
     for (int j = 0; j < m; ++j) t.rows.push_back(RowInfo{n + j, 0, j, 0});
-    kvr_status st = run_pass(c, t, s);
+    kvr_status st = run_pass(c, t, s, -1, nullptr, true);
     if (st != KVR_OK) return st;
     const SkinnyPlan plan = plan_skinny(V / 16, D, SCORE_ROWS, false, 16, "KVR_NT_LM", "KVR_SPLIT_LM");
 #define KVR_SCHECK(expr, what, step)                                                \
@@ -682,23 +720,18 @@ kvr_status score_block(kvr_ctx *c, void *cache, int n, int n_cap, const int32_t 
     } while (0)
     for (int c0 = 0; c0 < m; c0 += SCORE_ROWS) {
         const int R = std::min(SCORE_ROWS, m - c0);
-        const float *Y = c->score_y + (size_t)c0 * D;
+        // c0 is a multiple of 16 rows: the block starts at c0 * D in both layouts
+        const size_t x0 = (size_t)c0 * D * (c->bf16 ? 2 : 4);
+        const char *X = (const char *)c->Xn + x0, *X_lo = c->bf16 ? (const char *)c->Xn_lo + x0 : nullptr;
         int nsplit = 1;
         if (c->lm_pk) {
-            KVR_SCHECK(launch_to_operand(true, true, Y, R, D, c->Xn, c->Xn_lo, s), "lm_head operand", ST_LMHEAD);
-            KVR_SCHECK(skinny(EPI_STORE, c->Xn, c->Xn_lo, R, D, V, c->lm_pk, 1, c->score_part, nullptr, plan, s),
+            KVR_SCHECK(skinny(EPI_STORE, X, X_lo, R, D, V, c->lm_pk, 1, c->score_part, nullptr, plan, s),
                        "lm_head", ST_LMHEAD);
             nsplit = plan.split;
-        } else if (c->bf16) {
-            KVR_SCHECK(launch_to_operand(true, false, Y, R, D, c->Xn, c->Xn_lo, s), "lm_head operand", ST_LMHEAD);
-            KVR_SCHECK(launch_linear_generic(true, EPI_STORE, make_args(c->Xn, c->Xn_lo, D, R, D, V, c->lm_head,
-                                                                       c->lm_head, c->lm_head, V, V, nullptr,
-                                                                       c->score_part, nullptr, V), s),
-                       "lm_head", ST_LMHEAD);
         } else {
-            KVR_SCHECK(launch_linear_generic(false, EPI_STORE, make_args(Y, nullptr, D, R, D, V, c->lm_head, c->lm_head,
-                                                                        c->lm_head, V, V, nullptr, c->score_part,
-                                                                        nullptr, V), s),
+            KVR_SCHECK(launch_linear_generic(c->bf16, EPI_STORE, make_args(X, X_lo, D, R, D, V, c->lm_head, c->lm_head,
+                                                                          c->lm_head, V, V, nullptr, c->score_part,
+                                                                          nullptr, V), s),
                        "lm_head", ST_LMHEAD);
         }
         const int nt = lp ? std::max(0, std::min(R, m - 1 - c0)) : 0;  // rows with a target to score
@@ -711,19 +744,17 @@ kvr_status score_block(kvr_ctx *c, void *cache, int n, int n_cap, const int32_t 
 }
 
 kvr_status score_buffers(kvr_ctx *c) {
-    if (c->score_y) return KVR_OK;
+    if (c->score_part) return KVR_OK;
     const kvr_dims &d = c->d;
     const SkinnyPlan plan = plan_skinny(d.vocab / 16, d.d_model, SCORE_ROWS, false, 16, "KVR_NT_LM", "KVR_SPLIT_LM");
-    const size_t y_bytes = align_up((size_t)c->rows_cap * d.d_model * 4, 256);
     const size_t p_bytes = align_up((size_t)std::max(plan.split, 1) * SCORE_ROWS * d.vocab * 4, 256);
     const size_t l_bytes = logsoftmax_ws_bytes(SCORE_ROWS, d.vocab);
     char *buf = nullptr;
-    hipError_t e = hipMalloc((void **)&buf, y_bytes + p_bytes + l_bytes);
+    hipError_t e = hipMalloc((void **)&buf, p_bytes + l_bytes);
     if (e != hipSuccess) return fail(c, KVR_E_NOMEM, "scoring buffer allocation failed");
-    c->score_y = (float *)buf;
-    c->score_part = (float *)(buf + y_bytes);
-    c->score_lsm = buf + y_bytes + p_bytes;
-    c->score_bytes = y_bytes + p_bytes + l_bytes;
+    c->score_part = (float *)buf;
+    c->score_lsm = buf + p_bytes;
+    c->score_bytes = p_bytes + l_bytes;
     return KVR_OK;
 }
 
@@ -953,7 +984,7 @@ void kvr_destroy(kvr_ctx *c) {
         if (c->ws) (void)hipFree(c->ws);
         if (c->wpk) (void)hipFree(c->wpk);
         if (c->lm_pk) (void)hipFree(c->lm_pk);
-        if (c->score_y) (void)hipFree(c->score_y);
+        if (c->score_part) (void)hipFree(c->score_part);
         if (c->sel_scratch) (void)hipFree(c->sel_scratch);
     }
     delete c;

@@ -14,48 +14,6 @@ __device__ __forceinline__ float warp_sum(float v) {
     return v;
 }
 
-// Sum over a 256-thread block.
-__device__ __forceinline__ float block_sum256(float v, float *red) {
-    v = warp_sum(v);
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    if (l == 0) red[w] = v;
-    __syncthreads();
-    float t = red[0] + red[1] + red[2] + red[3];
-    __syncthreads();
-    return t;
-}
-
-// Token ids outside [0, vocab) are clamped into range rather than read out of
-// bounds.  Rows are copied in 16-byte chunks when d allows it (the table and H
-// are 16-byte aligned).
-template <typename TW>
-__global__ __launch_bounds__(256) void embed_kernel(const RowInfo *rows, const DocInfo *docs, const TW *embed,
-                                                    int d, int vocab, float *H) {
-    constexpr int V = 16 / sizeof(TW);  // table elements per chunk
-    const int r = blockIdx.x;
-    const RowInfo ri = rows[r];
-    const int tok = min(max(docs[ri.doc].tokens[ri.pos], 0), vocab - 1);
-    const TW *src = embed + (size_t)tok * d;
-    float *dst = H + (size_t)r * d;
-    if (d % V != 0) {
-        for (int i = threadIdx.x; i < d; i += 256) dst[i] = to_f32(src[i]);
-        return;
-    }
-    for (int i = threadIdx.x; i < d / V; i += 256) {
-        const u32x4 u = *reinterpret_cast<const u32x4 *>(src + (size_t)i * V);
-        if constexpr (sizeof(TW) == 2) {
-            float4 *o = reinterpret_cast<float4 *>(dst + (size_t)i * V);
-            o[0] = make_float4(__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xffff0000u),
-                               __uint_as_float(u[1] << 16), __uint_as_float(u[1] & 0xffff0000u));
-            o[1] = make_float4(__uint_as_float(u[2] << 16), __uint_as_float(u[2] & 0xffff0000u),
-                               __uint_as_float(u[3] << 16), __uint_as_float(u[3] & 0xffff0000u));
-        } else {
-            *reinterpret_cast<u32x4 *>(dst + (size_t)i * V) = u;
-        }
-    }
-}
-
-// Sum over a 1024-thread block.
 __device__ __forceinline__ float block_sum1024(float v, float *red) {
     v = warp_sum(v);
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
@@ -114,15 +72,46 @@ __device__ __forceinline__ void store_operand4(T *hi, T *lo, size_t off, const f
     }
 }
 
+// Where a normalised row goes: the next projection's operand (row-major or
+// operand order), after which the residual row is needed again, or the
+// caller's hidden row (null: nobody reads it), after the last layer.
+template <typename TO, bool PERM>
+struct OperandOut {
+    static constexpr bool KEEP_H = true;
+    TO *X, *X_lo;
+    int ldx;
+    __device__ __forceinline__ bool begin(int) { return true; }
+    __device__ __forceinline__ void put(int r, int c, int d, const float (&x)[4]) const {
+        store_operand4(X, X_lo, PERM ? perm_offset(r, c, d) : (size_t)r * ldx + c, x);
+    }
+};
+struct HiddenOut {
+    static constexpr bool KEEP_H = false;
+    const RowInfo *rows;
+    const DocInfo *docs;
+    float *dst;
+    __device__ __forceinline__ bool begin(int r) {
+        const RowInfo ri = rows[r];
+        dst = docs[ri.doc].hidden_out;
+        out = ri.out;
+        return dst != nullptr;
+    }
+    __device__ __forceinline__ void put(int, int c, int d, const float (&x)[4]) const {
+        *reinterpret_cast<float4 *>(dst + (size_t)out * d + c) = make_float4(x[0], x[1], x[2], x[3]);
+    }
+    int out;
+};
+
 // H[r] += sum of the split-K partial tiles (fixed order), then
-// X = H * rsqrt(mean(H^2) + eps) * gain in the operand type (row-major or
-// operand order).  One 1024-thread block per row; the row stays in registers
-// between the two passes (four columns per thread per pass, d % 4 == 0).
-template <typename TO, typename TG, bool PERM>
+// H * rsqrt(mean(H^2) + eps) * gain to `o`.  One 1024-thread block per row;
+// the row stays in registers between the two passes (four columns per thread
+// per pass, d % 4 == 0).  After the last layer H is not written back.
+template <typename TG, typename OUT>
 __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *part, int nsplit, int R,
-                                                       const TG *gain, int d, float eps, TO *X, TO *X_lo, int ldx) {
+                                                       const TG *gain, int d, float eps, OUT o) {
     __shared__ float red[16];
     const int r = blockIdx.x;
+    if (!o.begin(r)) return;
     float *h = H + (size_t)r * d;
     float4 v[NORM_V];
     float ss = 0.f;
@@ -133,7 +122,7 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *pa
         v[k] = *reinterpret_cast<const float4 *>(h + 4 * i);
         if (nsplit) {
             v[k] = add_partials(v[k], part, nsplit, R, r, d, i);
-            *reinterpret_cast<float4 *>(h + 4 * i) = v[k];
+            if (OUT::KEEP_H) *reinterpret_cast<float4 *>(h + 4 * i) = v[k];
         }
         ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
     }
@@ -146,24 +135,23 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *pa
         const int c = 4 * i;
         const float x[4] = {v[k].x * inv * to_f32(gain[c]), v[k].y * inv * to_f32(gain[c + 1]),
                             v[k].z * inv * to_f32(gain[c + 2]), v[k].w * inv * to_f32(gain[c + 3])};
-        store_operand4(X, X_lo, PERM ? perm_offset(r, c, d) : (size_t)r * ldx + c, x);
+        o.put(r, c, d, x);
     }
 }
 
-// The same for many rows with at most two partial tiles (prefill, batched
-// repair): one wavefront per row, each lane holding NV float4 of it, so that
-// the row and its partial tiles are loaded in one round (NV + NV loads in
-// flight per lane) and no block barrier is needed.  A 1024-thread block per
-// row keeps one load per thread in flight and waits at two barriers; at
-// 5000 rows that kernel ran at 3.4 TB/s.  Results are bit-identical to it
-// (d <= 4096, where it holds one float4 per thread).
-template <typename TO, typename TG, bool PERM, int NV>
+// The same for many rows with few partial tiles (prefill, batched repair):
+// one wavefront per row, each lane holding NV float4 of it, so that the row
+// and a partial tile are loaded in one round (NV + NV loads in flight per
+// lane) and no block barrier is needed.  A 1024-thread block per row keeps one
+// load per thread in flight and waits at two barriers; at 5000 rows that
+// kernel ran at 3.4 TB/s.  Results are bit-identical to it (d <= 4096, where
+// it holds one float4 per thread).
+template <typename TG, typename OUT, int NV>
 __global__ __launch_bounds__(512) void rmsnorm_wave_kernel(float *H, const float *part, int nsplit, int R,
-                                                           const TG *gain, int d, float eps, TO *X, TO *X_lo,
-                                                           int ldx) {
+                                                           const TG *gain, int d, float eps, OUT o) {
     const int lane = threadIdx.x & 63;
     const int r = blockIdx.x * 8 + (threadIdx.x >> 6);
-    if (r >= R) return;
+    if (r >= R || !o.begin(r)) return;
     float *h = H + (size_t)r * d;
     float4 v[NV], p[NV];
 #pragma unroll
@@ -195,7 +183,7 @@ __global__ __launch_bounds__(512) void rmsnorm_wave_kernel(float *H, const float
         const int c = 4 * (lane + 64 * k);
         float t = 0.f;
         if (c < d) {
-            if (nsplit) *reinterpret_cast<float4 *>(h + c) = v[k];
+            if (OUT::KEEP_H && nsplit) *reinterpret_cast<float4 *>(h + c) = v[k];
             t = v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
         }
         ss += warp_sum(t);
@@ -207,40 +195,7 @@ __global__ __launch_bounds__(512) void rmsnorm_wave_kernel(float *H, const float
         if (c >= d) continue;
         const float x[4] = {v[k].x * inv * to_f32(gain[c]), v[k].y * inv * to_f32(gain[c + 1]),
                             v[k].z * inv * to_f32(gain[c + 2]), v[k].w * inv * to_f32(gain[c + 3])};
-        store_operand4(X, X_lo, PERM ? perm_offset(r, c, d) : (size_t)r * ldx + c, x);
-    }
-}
-
-template <typename TG>
-__global__ __launch_bounds__(1024) void final_norm_kernel(float *H, const float *part, int nsplit, int R,
-                                                          const TG *gain, const RowInfo *rows, const DocInfo *docs,
-                                                          int d, float eps) {
-    __shared__ float red[16];
-    const int r = blockIdx.x;
-    const RowInfo ri = rows[r];
-    float *dst = docs[ri.doc].hidden_out;
-    float *h = H + (size_t)r * d;
-    float ss = 0.f;
-    for (int i = threadIdx.x; 4 * i < d; i += 1024) {
-        float4 v = *reinterpret_cast<const float4 *>(h + 4 * i);
-        if (nsplit) {
-            v = add_partials(v, part, nsplit, R, r, d, i);
-            *reinterpret_cast<float4 *>(h + 4 * i) = v;
-        }
-        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-    }
-    ss = block_sum1024(ss, red);
-    if (!dst) return;
-    dst += (size_t)ri.out * d;
-    const float inv = rsqrtf(ss / (float)d + eps);
-    for (int i = threadIdx.x; 4 * i < d; i += 1024) {
-        const float4 v = *reinterpret_cast<const float4 *>(h + 4 * i);
-        float4 o;
-        o.x = v.x * inv * to_f32(gain[4 * i]);
-        o.y = v.y * inv * to_f32(gain[4 * i + 1]);
-        o.z = v.z * inv * to_f32(gain[4 * i + 2]);
-        o.w = v.w * inv * to_f32(gain[4 * i + 3]);
-        *reinterpret_cast<float4 *>(dst + 4 * i) = o;
+        o.put(r, c, d, x);
     }
 }
 
@@ -342,6 +297,66 @@ __global__ __launch_bounds__(256) void resid_gain_kernel(float *H, const float *
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
     __syncthreads();
     if (threadIdx.x == 0) ssq[(size_t)b * R + r] = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// The first kernel of a pass: H[r] = embed[token of row r] and, when the first
+// projections apply the RMS scale (GAIN), layer 0's X = H * gain and sums of
+// squares as resid_gain_kernel makes them, by (row, 1024-column block).  Token
+// ids outside [0, vocab) are clamped into range rather than read out of
+// bounds.
+//
+// The pass's tables may still be in pinned host memory: the blocks past
+// `row_blocks` then copy them to the device while the others run, and the row
+// kernels' blocks take their rows from the kernel argument (one document, up
+// to EMBED_ROWS rows) or from host memory.  A copy, the embedding and the
+// first norm were three launches of about 4 us and a boundary each.
+template <typename TW, bool GAIN>
+__global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a, const TW *embed, const TW *gain, int d, int vocab,
+                                                    float *H, bf16_t *X, bf16_t *X_lo, float *ssq) {
+    if ((int)blockIdx.x >= a.row_blocks) {
+        const int i = ((int)blockIdx.x - a.row_blocks) * 256 + (int)threadIdx.x;
+        if (i < a.upload_16) a.upload_dst[i] = a.upload_src[i];
+        return;
+    }
+    __shared__ float red[4];
+    const int nb = (d + 1023) >> 10;
+    const int r = blockIdx.x / nb, b = blockIdx.x - r * nb;
+    const int32_t *tokens = a.tokens;
+    int pos;
+    if (tokens) {
+        pos = a.pos[r];
+    } else {
+        const RowInfo ri = a.rows[r];
+        pos = ri.pos;
+        tokens = a.docs[ri.doc].tokens;
+    }
+    const int tok = min(max(tokens[pos], 0), vocab - 1);
+    const int c = b * 1024 + 4 * (int)threadIdx.x;  // d is a multiple of four
+    float ss = 0.f;
+    if (c < d) {
+        const TW *src = embed + (size_t)tok * d + c;
+        float4 h;
+        if constexpr (sizeof(TW) == 2) {
+            const uint2 u = *reinterpret_cast<const uint2 *>(src);
+            h = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                            __uint_as_float(u.y & 0xffff0000u));
+        } else {
+            h = *reinterpret_cast<const float4 *>(src);
+        }
+        *reinterpret_cast<float4 *>(H + (size_t)r * d + c) = h;
+        if constexpr (GAIN) {
+            ss = h.x * h.x + h.y * h.y + h.z * h.z + h.w * h.w;
+            const float x[4] = {h.x * to_f32(gain[c]), h.y * to_f32(gain[c + 1]), h.z * to_f32(gain[c + 2]),
+                                h.w * to_f32(gain[c + 3])};
+            store_operand4(X, X_lo, perm_offset(r, c, d), x);
+        }
+    }
+    if constexpr (GAIN) {
+        ss = warp_sum(ss);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+        __syncthreads();
+        if (threadIdx.x == 0) ssq[(size_t)b * a.R + r] = ((red[0] + red[1]) + red[2]) + red[3];
+    }
 }
 
 // Four values of row-major type T at p (8-byte or 16-byte store).
@@ -446,42 +461,51 @@ __global__ __launch_bounds__(256) void rope_scatter_vec_kernel(const float *qkv,
 
 }  // namespace
 
-hipError_t launch_embed(bool bf16, const RowInfo *rows, const DocInfo *docs, int R, const void *embed, int d,
-                        int vocab, float *H, hipStream_t s) {
-    if (R <= 0) return hipSuccess;
-    if (bf16)
-        kvr_launch(embed_kernel<bf16_t>, dim3(R), dim3(256), 0, s, rows, docs, (const bf16_t *)embed, d, vocab,
-                           H);
+hipError_t launch_embed(bool bf16, const EmbedArgs &args, const void *embed, const void *gain, int d, int vocab, float *H,
+                        void *X, void *X_lo, float *ssq, hipStream_t s) {
+    if (args.R <= 0) return hipSuccess;
+    if (d % 4 != 0 || (gain && (!bf16 || d % 32 != 0 || !X || !X_lo || !ssq))) return hipErrorInvalidValue;
+    EmbedArgs a = args;
+    a.row_blocks = a.R * resid_gain_blocks(d);
+    const dim3 grid(a.row_blocks + (a.upload_16 + 255) / 256);
+    if (bf16 && gain)
+        kvr_launch((embed_kernel<bf16_t, true>), grid, dim3(256), 0, s, a, (const bf16_t *)embed, (const bf16_t *)gain, d,
+                   vocab, H, (bf16_t *)X, (bf16_t *)X_lo, ssq);
+    else if (bf16)
+        kvr_launch((embed_kernel<bf16_t, false>), grid, dim3(256), 0, s, a, (const bf16_t *)embed, (const bf16_t *)nullptr,
+                   d, vocab, H, (bf16_t *)nullptr, (bf16_t *)nullptr, (float *)nullptr);
     else
-        kvr_launch(embed_kernel<float>, dim3(R), dim3(256), 0, s, rows, docs, (const float *)embed, d, vocab,
-                           H);
+        kvr_launch((embed_kernel<float, false>), grid, dim3(256), 0, s, a, (const float *)embed, (const float *)nullptr, d,
+                   vocab, H, (bf16_t *)nullptr, (bf16_t *)nullptr, (float *)nullptr);
     return hipGetLastError();
 }
 
-hipError_t launch_rmsnorm(bool bf16_out, bool bf16_gain, float *H, const float *part, int nsplit, const void *gain,
-                          int R, int d, float eps, void *X, void *X_lo, int ldx, bool perm, hipStream_t s) {
-    if (R <= 0) return hipSuccess;
-    if (d % 4 != 0 || d > 4 * 1024 * NORM_V || (!perm && ldx % 4 != 0)) return hipErrorInvalidValue;
-    // many rows and at most two partial tiles: a wavefront per row (d <= 4096)
-    if (bf16_out && bf16_gain && perm && R >= 512 && nsplit <= 2 && d <= 4096) {
-        kvr_launch((rmsnorm_wave_kernel<bf16_t, bf16_t, true, 16>), dim3((R + 7) / 8), dim3(512), 0, s, H, part, nsplit,
-                   R, (const bf16_t *)gain, d, eps, (bf16_t *)X, (bf16_t *)X_lo, ldx);
-        return hipGetLastError();
-    }
-    if (bf16_out && bf16_gain) {
-        if (perm)
-            kvr_launch((rmsnorm_kernel<bf16_t, bf16_t, true>), dim3(R), dim3(1024), 0, s, H, part, nsplit, R,
-                               (const bf16_t *)gain, d, eps, (bf16_t *)X, (bf16_t *)X_lo, ldx);
-        else
-            kvr_launch((rmsnorm_kernel<bf16_t, bf16_t, false>), dim3(R), dim3(1024), 0, s, H, part, nsplit, R,
-                               (const bf16_t *)gain, d, eps, (bf16_t *)X, (bf16_t *)X_lo, ldx);
-    } else if (!bf16_out && !bf16_gain && !perm) {
-        kvr_launch((rmsnorm_kernel<float, float, false>), dim3(R), dim3(1024), 0, s, H, part, nsplit, R,
-                           (const float *)gain, d, eps, (float *)X, (float *)nullptr, ldx);
+// Many rows and few partial tiles: a wavefront per row (d <= 4096).  Its blocks
+// of eight rows leave units idle below a thousand rows (528 rows, three
+// partial tiles: 21 us, 25 us in blocks of one row, against 17 us).
+template <typename TG, typename OUT>
+static hipError_t launch_norm(float *H, const float *part, int nsplit, const TG *gain, int R, int d, float eps, OUT o,
+                              hipStream_t s) {
+    if (R >= 1024 && nsplit <= 3 && d <= 4096) {
+        kvr_launch((rmsnorm_wave_kernel<TG, OUT, 16>), dim3((R + 7) / 8), dim3(512), 0, s, H, part, nsplit, R, gain, d, eps,
+                   o);
     } else {
-        return hipErrorInvalidValue;
+        kvr_launch((rmsnorm_kernel<TG, OUT>), dim3(R), dim3(1024), 0, s, H, part, nsplit, R, gain, d, eps, o);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_rmsnorm(bool bf16, float *H, const float *part, int nsplit, const void *gain, int R, int d, float eps,
+                          void *X, void *X_lo, int ldx, bool perm, hipStream_t s) {
+    if (R <= 0) return hipSuccess;
+    if (d % 4 != 0 || d > 4 * 1024 * NORM_V || (!perm && ldx % 4 != 0) || (!bf16 && perm)) return hipErrorInvalidValue;
+    if (!bf16)
+        return launch_norm(H, part, nsplit, (const float *)gain, R, d, eps, OperandOut<float, false>{(float *)X, nullptr, ldx}, s);
+    if (perm)
+        return launch_norm(H, part, nsplit, (const bf16_t *)gain, R, d, eps,
+                           OperandOut<bf16_t, true>{(bf16_t *)X, (bf16_t *)X_lo, ldx}, s);
+    return launch_norm(H, part, nsplit, (const bf16_t *)gain, R, d, eps,
+                       OperandOut<bf16_t, false>{(bf16_t *)X, (bf16_t *)X_lo, ldx}, s);
 }
 
 int resid_gain_blocks(int d) { return (d + 1023) / 1024; }
@@ -503,14 +527,10 @@ hipError_t launch_resid_gain(bool bf16_gain, float *H, const float *part, int ns
 hipError_t launch_final_norm(bool bf16_gain, float *H, const float *part, int nsplit, const void *gain,
                              const RowInfo *rows, const DocInfo *docs, int R, int d, float eps, hipStream_t s) {
     if (R <= 0) return hipSuccess;
-    if (d % 4 != 0) return hipErrorInvalidValue;
-    if (bf16_gain)
-        kvr_launch(final_norm_kernel<bf16_t>, dim3(R), dim3(1024), 0, s, H, part, nsplit, R,
-                           (const bf16_t *)gain, rows, docs, d, eps);
-    else
-        kvr_launch(final_norm_kernel<float>, dim3(R), dim3(1024), 0, s, H, part, nsplit, R,
-                           (const float *)gain, rows, docs, d, eps);
-    return hipGetLastError();
+    if (d % 4 != 0 || d > 4 * 1024 * NORM_V) return hipErrorInvalidValue;
+    const HiddenOut o{rows, docs, nullptr, 0};
+    if (bf16_gain) return launch_norm(H, part, nsplit, (const bf16_t *)gain, R, d, eps, o, s);
+    return launch_norm(H, part, nsplit, (const float *)gain, R, d, eps, o, s);
 }
 
 hipError_t launch_rope_scatter(bool bf16, const float *qkv, int nsplit, const void *bq, const void *bk,

@@ -1,5 +1,4 @@
-// Row kernels of the scoring forward: hidden rows -> LM-head operand, and the
-// log-softmax over the vocabulary with the teacher-forced target gather and
+// Row kernels of the scoring forward: the log-softmax over the vocabulary with the teacher-forced target gather and
 // the greedy argmax.
 #include <math.h>
 
@@ -10,15 +9,6 @@
 namespace kvr {
 
 namespace {
-
-// X = Y rows [0, R) (fp32, row stride d) as the LM head's operand: a
-// compensated bf16 pair in operand order (PERM) or row-major, or fp32.
-template <typename TO, bool PERM>
-__global__ __launch_bounds__(256) void to_operand_kernel(const float *Y, int d, TO *X, TO *X_lo) {
-    const int r = blockIdx.x;
-    for (int c = threadIdx.x; c < d; c += 256)
-        store_operand(X, X_lo, PERM ? perm_offset(r, c, d) : (size_t)r * d + c, Y[(size_t)r * d + c]);
-}
 
 // Log-softmax in two stages so that a few rows still spread over the chip.
 // The logits of row r are z[v] = sum of the `nsplit` fp32 tiles part[s][r][V]
@@ -112,14 +102,6 @@ constexpr int LSM_MAXC = 64;     // chunks per row at most
 int lsm_chunks(int V) { return std::min(LSM_MAXC, std::max(1, (V + LSM_CHUNK - 1) / LSM_CHUNK)); }
 
 }  // namespace
-
-hipError_t launch_to_operand(bool bf16, bool perm, const float *Y, int R, int d, void *X, void *X_lo, hipStream_t s) {
-    if (R <= 0) return hipSuccess;
-    if (bf16 && perm) kvr_launch((to_operand_kernel<bf16_t, true>), dim3(R), dim3(256), 0, s, Y, d, (bf16_t *)X, (bf16_t *)X_lo);
-    else if (bf16) kvr_launch((to_operand_kernel<bf16_t, false>), dim3(R), dim3(256), 0, s, Y, d, (bf16_t *)X, (bf16_t *)X_lo);
-    else kvr_launch((to_operand_kernel<float, false>), dim3(R), dim3(256), 0, s, Y, d, (float *)X, (float *)nullptr);
-    return hipGetLastError();
-}
 
 size_t logsoftmax_ws_bytes(int R, int V) { return (size_t)R * lsm_chunks(V) * sizeof(LsmStat); }
 

@@ -153,3 +153,51 @@ def test_tiled_row_tiles(monkeypatch, rt):
     row) and the planned one; the repair's projections are cut into K slices of unequal length."""
     monkeypatch.setenv("KVR_TILED_RT", rt)
     prefill_and_repair(TILED, BF16, 785, (301, 317), 234, "random", seed=2)
+
+
+# rows, documents: the first kernel takes positions from its argument, or reads the tables from host memory (several
+# documents, more rows than the argument holds), or finds them on the device (tables too large to be uploaded by it)
+@pytest.mark.parametrize("K,docs", [(20, 1), (20, 3), (300, 1), (1500, 3)], ids=["argument", "documents", "rows", "copied"])
+def test_pass_tables_and_graph_replay(K, docs):
+    """A repair captured into a graph (relaxed mode) and replayed, with eager repairs of the same edits and
+    synchronisations between the replays: every replay equals the eager result bit for bit."""
+    shape = synth.ModelShape("tables", 2, 256, 4, 2, 64, 256, 256, 1e-5, 10000.0)
+    n = 2000
+    w = synth.make_weights(shape, dtype=torch.bfloat16, seed=3)
+    eng = Engine(shape, to_device_weights(w), BF16, max_ctx=n, max_rows=docs * (K + 16))
+    try:
+        toks = [synth.make_tokens(n, shape.vocab, seed=7 + i).cuda() for i in range(docs)]
+        stale = [synth.make_stale_cache(shape, n, label=i).cuda() for i in range(docs)]
+        caches = [s.clone() for s in stale]
+        hidden = [torch.zeros((K + 16, shape.d_model), device="cuda") for _ in range(docs)]
+        A = osel.select_random(n, 100, 116, K, 1)
+        jobs = [dict(cache=c, tokens=t, edit_start=100, edit_end=116, positions=A, hidden=h)
+                for c, t, h in zip(caches, toks, hidden)]
+        say(f"case: eager repair of {docs} x {K + 16} rows")
+        eng.repair(jobs)
+        torch.cuda.synchronize()
+        want = [h.clone() for h in hidden]
+        ow = OracleWeights(w, cache=True)
+        for i in range(docs):
+            ref = stale[i].to(torch.float64).cpu().numpy()
+            y = od.repair(shape, ow, ref, toks[i].cpu().numpy(), 100, 116, A)
+            compare_repair(shape, None, stale[i], caches[i], hidden[i], ref, y, od.repaired_set(100, 116, A), n, TOL[BF16],
+                           f"document {i}")
+        say("case: captured repair")
+        g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.graph(g, stream=side, capture_error_mode="relaxed"):
+            eng.repair(jobs)
+        for k in range(4):
+            for c, s, h in zip(caches, stale, hidden):
+                c.copy_(s)
+                h.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(hidden, want)), f"replay {k}"
+            eng.repair(jobs)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(hidden, want)), f"eager after replay {k}"
+        del g
+    finally:
+        eng.close()
