@@ -2,6 +2,8 @@
 // embedding + cache scatter).
 #include <math.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace kvr {
@@ -14,15 +16,15 @@ __device__ __forceinline__ float warp_sum(float v) {
     return v;
 }
 
-__device__ __forceinline__ float block_sum1024(float v, float *red) {
+// Sum over a block of up to 16 wavefronts, in wavefront order.
+__device__ __forceinline__ float block_sum(float v, float *red) {
     v = warp_sum(v);
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, nw = blockDim.x >> 6;
     if (l == 0) red[w] = v;
     __syncthreads();
     float t = 0.f;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) t += red[q];
-    __syncthreads();
+    for (int q = 0; q < 16; ++q) t += q < nw ? red[q] : 0.f;
     return t;
 }
 
@@ -103,9 +105,10 @@ struct HiddenOut {
 };
 
 // H[r] += sum of the split-K partial tiles (fixed order), then
-// H * rsqrt(mean(H^2) + eps) * gain to `o`.  One 1024-thread block per row;
-// the row stays in registers between the two passes (four columns per thread
-// per pass, d % 4 == 0).  After the last layer H is not written back.
+// H * rsqrt(mean(H^2) + eps) * gain to `o`.  One block per row, as many
+// wavefronts as the row has 256-column pieces, at most 16; the row stays in
+// registers between the two passes (four columns per thread per pass, d % 4
+// == 0).  After the last layer H is not written back.
 template <typename TG, typename OUT>
 __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *part, int nsplit, int R,
                                                        const TG *gain, int d, float eps, OUT o) {
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *pa
     float ss = 0.f;
 #pragma unroll
     for (int k = 0; k < NORM_V; ++k) {
-        const int i = threadIdx.x + 1024 * k;
+        const int i = threadIdx.x + blockDim.x * k;
         if (4 * i >= d) break;
         v[k] = *reinterpret_cast<const float4 *>(h + 4 * i);
         if (nsplit) {
@@ -126,11 +129,11 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *pa
         }
         ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
     }
-    ss = block_sum1024(ss, red);
+    ss = block_sum(ss, red);
     const float inv = rsqrtf(ss / (float)d + eps);
 #pragma unroll
     for (int k = 0; k < NORM_V; ++k) {
-        const int i = threadIdx.x + 1024 * k;
+        const int i = threadIdx.x + blockDim.x * k;
         if (4 * i >= d) break;
         const int c = 4 * i;
         const float x[4] = {v[k].x * inv * to_f32(gain[c]), v[k].y * inv * to_f32(gain[c + 1]),
@@ -490,7 +493,8 @@ static hipError_t launch_norm(float *H, const float *part, int nsplit, const TG 
         kvr_launch((rmsnorm_wave_kernel<TG, OUT, 16>), dim3((R + 7) / 8), dim3(512), 0, s, H, part, nsplit, R, gain, d, eps,
                    o);
     } else {
-        kvr_launch((rmsnorm_kernel<TG, OUT>), dim3(R), dim3(1024), 0, s, H, part, nsplit, R, gain, d, eps, o);
+        const int threads = std::min(1024, (d / 4 + 63) / 64 * 64);
+        kvr_launch((rmsnorm_kernel<TG, OUT>), dim3(R), dim3(threads), 0, s, H, part, nsplit, R, gain, d, eps, o);
     }
     return hipGetLastError();
 }
