@@ -194,7 +194,13 @@ size_t elem_size(const kvr_dims &d) { return d.dtype == KVR_BF16 ? 2 : 4; }
 // target is one item per unit: more, shorter items cost a second round and a
 // longer combine (Mistral shape, 48 rows at 4900-4950: 0.92 ms of attention
 // and combine per repair at 768 items against 0.64 ms at 256).
-void plan_attention(const kvr_ctx *c, Tables &t) {
+//
+// The generic kernel's blocks are smaller (four wavefronts, 35 KB of LDS at
+// head_dim 64: four to a unit; two at 128), and an item of 64 rows reads each
+// key for all of them: with enough row blocks it keeps them whole and takes
+// key ranges for two to four blocks per unit (1501-token fp32 prefill, 4
+// heads: 235 -> 213 us a call against one-tile items, one per unit).
+void plan_attention(const kvr_ctx *c, Tables &t, bool mfma) {
     const int Hkv = c->d.n_kv_heads;
     const int G = c->d.n_heads / Hkv;
     using Block = Tables::Block;
@@ -219,8 +225,12 @@ void plan_attention(const kvr_ctx *c, Tables &t) {
     // read the same K/V tiles (from L2), each row's keys are cut into fewer
     // parts (fewer partials to write and combine), and an item of one tile
     // has few enough (head, row tile) pairs for the kernel's two key groups.
-    const bool split = (long long)blocks.size() * Hkv < target / 2;
-    if (split) {
+    bool split = (long long)blocks.size() * Hkv < target / 2;
+    if (!mfma && target_env <= 0 && (long long)blocks.size() * Hkv >= 64) {
+        const int per_item = (G * mt + 3) / 4;  // blocks of an item (a wavefront per (head, row tile) pair)
+        target = std::max(1, 256 * (c->d.head_dim > 64 ? 2 : 4) / per_item);
+        split = (long long)blocks.size() * Hkv < target / 2;
+    } else if (split) {
         mt = std::min(mt_max, std::max(1, env_int("KVR_ATT_MT", 1)));
         make_blocks(16 * mt);
     }
@@ -238,7 +248,7 @@ void plan_attention(const kvr_ctx *c, Tables &t) {
         // the units that finish early take the rest, and the last round is
         // short (attention 59.5 -> 48.0 us per layer; at 144 rows, 5-tile
         // items, the doubled target cost 17.1 -> 23.0 us)
-        if (target_env <= 0 && ks >= 12 * ATT_KT) {
+        if (mfma && target_env <= 0 && ks >= 12 * ATT_KT) {
             target *= 2;
             ks = (total_keys * Hkv + target - 1) / target;
         }
@@ -486,7 +496,7 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
     const bool attn_mfma = !c->force_simple && attention_mfma_ok(c->bf16, d.n_heads, d.n_kv_heads, d.head_dim);
     const bool sk = skinny_pass_ok(c, R);
     const bool op = c->wpk != nullptr;  // matrix operands in MFMA operand order (both packed-weight kernels)
-    plan_attention(c, t);
+    plan_attention(c, t, attn_mfma);
     if ((int)t.items.size() > c->items_cap || (int)t.comb.size() > c->comb_cap)
         return fail(c, KVR_E_RANGE, "attention plan exceeds the context's item capacity");
 

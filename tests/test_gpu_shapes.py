@@ -201,3 +201,11 @@ def test_pass_tables_and_graph_replay(K, docs):
         del g
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("dtype,hd,hq,hkv", [(F32, 64, 4, 4), (F32, 128, 8, 4), (BF16, 80, 12, 4)],
+                         ids=["f32-64", "f32-128", "bf16-80"])
+def test_generic_attention_many_rows(dtype, hd, hq, hkv):
+    """The generic kernel's planned items of 64 rows (their last row block holds 12 rows), split over the keys."""
+    shape = synth.ModelShape(f"generic attention {hd}x{hq}/{hkv}", 1, 64, hq, hkv, hd, 64, 128, 1e-5, 10000.0)
+    prefill_and_repair(shape, dtype, 1100, (700, 716), 250, "random", seed=hd)
