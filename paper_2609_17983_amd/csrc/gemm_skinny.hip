@@ -63,21 +63,42 @@ __global__ __launch_bounds__(256) void linear_skinny_kernel(SkinnyArgs a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) rs_pre[q] = a.rs_ssq[(size_t)min(q, a.rs_nb - 1) * a.R + threadIdx.x];
     }
-    const int split = a.split;
-    const int tg = blockIdx.x / split, sp = blockIdx.x - tg * split;
+    // K slice (fastest, so that with eight slices an XCD's blocks share one)
+    // and tile group.  No division stands in front of the first loads where
+    // the usual plans need none: power-of-two splits, tile-major weights, or
+    // groups of NT tiles (@DIV@).
+    const int split = a.split, sp = blockIdx.x, tg = blockIdx.y;
     const int ksteps = a.K >> 5;
     const int gw = sp * 4 + w, nw = split * 4;
-    const int s0 = (int)(((long long)ksteps * gw) / nw);
-    const int s1 = (int)(((long long)ksteps * (gw + 1)) / nw);
+    int s0 = ksteps * gw, s1 = ksteps * (gw + 1);
+    if ((nw & (nw - 1)) == 0) {
+        const int sh = __builtin_ctz(nw);
+        s0 >>= sh;
+        s1 >>= sh;
+    } else {
+        s0 /= nw;
+        s1 /= nw;
+    }
 
     // tiles past the end (last block of a ragged grid) re-read the last tile;
     // their results are never stored
     const bf16_t *wp[NT];
     int wstride[NT];  // elements between a tile's k-steps (packed_tile_offset)
+    if (a.grp <= 1 || a.grp == NT) {
+        const int gl = a.grp <= 1 ? 1 : min(NT, a.ntiles - tg * NT);  // tiles of the group
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-        wp[nt] = (const bf16_t *)a.w +
-                 packed_tile_offset(min(tg * NT + nt, a.ntiles - 1), a.ntiles, ksteps, a.grp, &wstride[nt]) + lane * 8;
+        for (int nt = 0; nt < NT; ++nt) {
+            const int t = min(nt, a.ntiles - 1 - tg * NT);  // tile within the block
+            wstride[nt] = gl * 512;
+            wp[nt] = (const bf16_t *)a.w +
+                     ((size_t)tg * NT * ksteps + (a.grp <= 1 ? (size_t)t * ksteps : (size_t)t)) * 512 + lane * 8;
+        }
+    } else {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            wp[nt] = (const bf16_t *)a.w +
+                     packed_tile_offset(min(tg * NT + nt, a.ntiles - 1), a.ntiles, ksteps, a.grp, &wstride[nt]) + lane * 8;
+    }
     const bf16_t *xp[MT], *xq[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -102,7 +123,7 @@ __global__ __launch_bounds__(256) void linear_skinny_kernel(SkinnyArgs a) {
         // order: rotation split that range and cost gate/up 1 %.  Logical step
         // lg maps to k-step phys(lg); steps past the slice re-read its last one.
         const int nks = s1 - s0;
-        const int rot = a.grp > 1 ? 0 : (int)((blockIdx.x >> 3) % (unsigned)nks);
+        const int rot = a.grp > 1 ? 0 : (int)((unsigned)((tg * split + sp) >> 3) % (unsigned)nks);
         auto phys = [&](int lg) {
             lg = min(lg, s1 - 1);
             int q = lg - s0 + rot;
@@ -230,7 +251,7 @@ __global__ __launch_bounds__(256) void linear_skinny_kernel(SkinnyArgs a) {
 
 template <int MT, int NT>
 hipError_t launch_mt_nt(int epi, const SkinnyArgs &a, hipStream_t s) {
-    dim3 grid(((a.ntiles + NT - 1) / NT) * a.split);
+    const dim3 grid(a.split, (a.ntiles + NT - 1) / NT);
     if (epi == EPI_SWIGLU) kvr_launch((linear_skinny_kernel<MT, NT, EPI_SWIGLU>), grid, dim3(256), 0, s, a);
     else kvr_launch((linear_skinny_kernel<MT, NT, EPI_STORE>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
