@@ -86,7 +86,7 @@ template <int HD, int PPW, int KG>
 __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t *Q, const bf16_t *Q_lo,
                                                                     const RowInfo *rows,
                                                                     const AttnItem *items, int layer, int Hq, int Hkv,
-                                                                    int MT, float *part, bf16_t *O, bf16_t *O_lo,
+                                                                    int G, int MT, float *part, bf16_t *O, bf16_t *O_lo,
                                                                     int o_perm, float *lse) {
     constexpr int KSTEPS = HD / 32, DTILES = HD / 16;  // k-steps of a score, 16-wide dimension tiles
     constexpr int CPR = HD / 8;                        // 16-byte chunks per cache row
@@ -106,7 +106,6 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
     const AttnItem it = items[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index (uniform)
-    const int G = Hq / Hkv;
     const int qd = Hq * HD;
     const int MTi = (it.nrows + 15) >> 4;  // row tiles this item has
     const int npairs = G * MTi;
@@ -130,8 +129,9 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
     for (int i = 0; i < PPW; ++i) {
         const int p = lw + WG * i;
         pvalid[i] = p < npairs;
-        pt[i] = pvalid[i] ? p / MTi : 0;
-        pm[i] = pvalid[i] ? p % MTi : 0;
+        // one row tile per item (split keys) needs no division in front of the loads
+        pt[i] = !pvalid[i] ? 0 : MTi == 1 ? p : p / MTi;
+        pm[i] = !pvalid[i] ? 0 : MTi == 1 ? 0 : p % MTi;
         const int r = pm[i] * 16 + (lane & 15);  // this lane's query row within the item
         prow[i] = (pvalid[i] && r < it.nrows) ? rows[it.row0 + r].pos : -1;
         const int qrow = it.row0 + min(r, it.nrows - 1);
@@ -465,13 +465,13 @@ static hipError_t launch_mfma_hd(const bf16_t *Q, const bf16_t *Q_lo, const RowI
     const int npairs = (Hq / Hkv) * MT;
     if (2 * npairs <= WAVES)
         kvr_launch((attention_mfma_kernel<HD, 1, 2>), dim3(n_items), dim3(64 * WAVES), 0, s, Q, Q_lo, rows, items, layer,
-                   Hq, Hkv, MT, part, O, O_lo, (int)o_perm, lse);
+                   Hq, Hkv, Hq / Hkv, MT, part, O, O_lo, (int)o_perm, lse);
     else if (npairs <= WAVES)
         kvr_launch((attention_mfma_kernel<HD, 1, 1>), dim3(n_items), dim3(64 * WAVES), 0, s, Q, Q_lo, rows, items, layer,
-                   Hq, Hkv, MT, part, O, O_lo, (int)o_perm, lse);
+                   Hq, Hkv, Hq / Hkv, MT, part, O, O_lo, (int)o_perm, lse);
     else if (npairs <= 2 * WAVES)
         kvr_launch((attention_mfma_kernel<HD, 2, 1>), dim3(n_items), dim3(64 * WAVES), 0, s, Q, Q_lo, rows, items, layer,
-                   Hq, Hkv, MT, part, O, O_lo, (int)o_perm, lse);
+                   Hq, Hkv, Hq / Hkv, MT, part, O, O_lo, (int)o_perm, lse);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) void linear_skinny_kernel(SkinnyArgs a) {
     if (s0 < s1) {
         // With tile-major weights every block walks its K slice from a
         // different starting k-step (rotated by the block's index within its
-        // XCD).  In lockstep the 32 blocks of an XCD ask for each activation
+        // XCD, 32 phases over the slice).  In lockstep the 32 blocks of an XCD ask for each activation
         // line at the same moment, and all of them wait for its first fetch;
         // rotated, one of them takes the miss and the others find the line in
         // L2 (8B shape, 48 rows: down 27.0 -> 25.8 us, QKV 15.8 -> 15.2 us).
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(256) void linear_skinny_kernel(SkinnyArgs a) {
         // order: rotation split that range and cost gate/up 1 %.  Logical step
         // lg maps to k-step phys(lg); steps past the slice re-read its last one.
         const int nks = s1 - s0;
-        const int rot = a.grp > 1 ? 0 : (int)((unsigned)((tg * split + sp) >> 3) % (unsigned)nks);
+        const int rot = a.grp > 1 ? 0 : ((((tg * split + sp) >> 3) & 31) * nks) >> 5;
         auto phys = [&](int lg) {
             lg = min(lg, s1 - 1);
             int q = lg - s0 + rot;

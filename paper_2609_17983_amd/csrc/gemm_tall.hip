@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256, 1) void linear_tall_kernel(LinearArgs a) {
     const int split = a.split > 1 ? a.split : 1;
     const int tg = blockIdx.x / split, sp = blockIdx.x - tg * split;
     const int ksteps = a.K >> 5;
-    const int s0 = (int)((long long)ksteps * sp / split), s1 = (int)((long long)ksteps * (sp + 1) / split);
+    const int s0 = ksteps * sp / split, s1 = ksteps * (sp + 1) / split;
     const int nk = s1 - s0;
     const int ntiles = (EPI == EPI_SWIGLU ? 2 * a.N : a.N) >> 4;
     const int t0 = tg * a.tpb, tend = min(t0 + a.tpb, ntiles);

@@ -425,7 +425,7 @@ __global__ __launch_bounds__(256) void rope_scatter_vec_kernel(const float *qkv,
     T *cache = (T *)dc.cache;
     const size_t head_stride = (size_t)dc.n_cap * hd;
     if (idx < nrot) {
-        const int j = idx / hq4, i = (idx - j * hq4) * 4;
+        const int j = (hq4 & (hq4 - 1)) == 0 ? idx >> __builtin_ctz(hq4) : idx / hq4, i = (idx - j * hq4) * 4;
         const bool isq = j < Hq;
         const int g = j - Hq;
         const int ca = isq ? j * hd + i : qd + g * hd + i;
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void rope_scatter_vec_kernel(const float *qkv,
             const float4 bb = load4_f32(bv + c4);
             v.x += bb.x; v.y += bb.y; v.z += bb.z; v.w += bb.w;
         }
-        const int g = c4 / hd, i = c4 - g * hd;
+        const int g = (hd & (hd - 1)) == 0 ? c4 >> __builtin_ctz(hd) : c4 / hd, i = c4 - g * hd;
         T *vb = cache + (((size_t)layer * 2 + 1) * Hkv + g) * head_stride + (size_t)ri.pos * hd;
         store4(vb + i, v);
     }
