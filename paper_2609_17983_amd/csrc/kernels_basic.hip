@@ -52,6 +52,14 @@ __device__ __forceinline__ float4 add_partials(float4 h, const float *part, int 
     return h;
 }
 
+// Four gains (8-byte or 16-byte aligned: d and the column are multiples of four).
+__device__ __forceinline__ float4 load_gain4(const float *g) { return *reinterpret_cast<const float4 *>(g); }
+__device__ __forceinline__ float4 load_gain4(const bf16_t *g) {
+    const uint2 u = *reinterpret_cast<const uint2 *>(g);
+    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                       __uint_as_float(u.y & 0xffff0000u));
+}
+
 constexpr int NORM_V = 4;  // float4 per thread of the row kernels: d <= 16384
 
 // Four consecutive outputs (columns c..c+3, c % 4 == 0) of an operand row;
@@ -116,12 +124,13 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *pa
     const int r = blockIdx.x;
     if (!o.begin(r)) return;
     float *h = H + (size_t)r * d;
-    float4 v[NORM_V];
+    float4 v[NORM_V], gn[NORM_V];
     float ss = 0.f;
 #pragma unroll
     for (int k = 0; k < NORM_V; ++k) {
         const int i = threadIdx.x + blockDim.x * k;
         if (4 * i >= d) break;
+        gn[k] = load_gain4(gain + 4 * i);
         v[k] = *reinterpret_cast<const float4 *>(h + 4 * i);
         if (nsplit) {
             v[k] = add_partials(v[k], part, nsplit, R, r, d, i);
@@ -135,10 +144,8 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *pa
     for (int k = 0; k < NORM_V; ++k) {
         const int i = threadIdx.x + blockDim.x * k;
         if (4 * i >= d) break;
-        const int c = 4 * i;
-        const float x[4] = {v[k].x * inv * to_f32(gain[c]), v[k].y * inv * to_f32(gain[c + 1]),
-                            v[k].z * inv * to_f32(gain[c + 2]), v[k].w * inv * to_f32(gain[c + 3])};
-        o.put(r, c, d, x);
+        const float x[4] = {v[k].x * inv * gn[k].x, v[k].y * inv * gn[k].y, v[k].z * inv * gn[k].z, v[k].w * inv * gn[k].w};
+        o.put(r, 4 * i, d, x);
     }
 }
 
@@ -278,15 +285,17 @@ __global__ __launch_bounds__(256) void resid_gain_kernel(float *H, const float *
     const int i = b * 256 + threadIdx.x;  // float4 index within the row
     float ss = 0.f;
     if (4 * i < d) {
+        // the gain is loaded with the row: after the store of H it would be a
+        // round trip of its own (the compiler cannot move it across the store)
         float *hp = H + (size_t)r * d + 4 * i;
         float4 h = *reinterpret_cast<const float4 *>(hp);
+        const float4 gn = load_gain4(gain + 4 * i);
         if (nsplit) {
             h = add_partials(h, part, nsplit, R, r, d, i);
             *reinterpret_cast<float4 *>(hp) = h;
         }
         ss = h.x * h.x + h.y * h.y + h.z * h.z + h.w * h.w;
-        const float4 x = {h.x * to_f32(gain[4 * i]), h.y * to_f32(gain[4 * i + 1]), h.z * to_f32(gain[4 * i + 2]),
-                          h.w * to_f32(gain[4 * i + 3])};
+        const float4 x = {h.x * gn.x, h.y * gn.y, h.z * gn.z, h.w * gn.w};
         const bf16_t hi[4] = {f32_to_bf16(x.x), f32_to_bf16(x.y), f32_to_bf16(x.z), f32_to_bf16(x.w)};
         const bf16_t lo[4] = {f32_to_bf16(x.x - bf16_to_f32(hi[0])), f32_to_bf16(x.y - bf16_to_f32(hi[1])),
                               f32_to_bf16(x.z - bf16_to_f32(hi[2])), f32_to_bf16(x.w - bf16_to_f32(hi[3]))};
@@ -346,11 +355,12 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a, const TW *embed
         } else {
             h = *reinterpret_cast<const float4 *>(src);
         }
+        float4 gn = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (GAIN) gn = load_gain4(gain + c);
         *reinterpret_cast<float4 *>(H + (size_t)r * d + c) = h;
         if constexpr (GAIN) {
             ss = h.x * h.x + h.y * h.y + h.z * h.z + h.w * h.w;
-            const float x[4] = {h.x * to_f32(gain[c]), h.y * to_f32(gain[c + 1]), h.z * to_f32(gain[c + 2]),
-                                h.w * to_f32(gain[c + 3])};
+            const float x[4] = {h.x * gn.x, h.y * gn.y, h.z * gn.z, h.w * gn.w};
             store_operand4(X, X_lo, perm_offset(r, c, d), x);
         }
     }
@@ -411,8 +421,6 @@ __global__ __launch_bounds__(256) void rope_scatter_vec_kernel(const float *qkv,
     const int N = qd + 2 * kd;
     const int nrot = (Hq + Hkv) * hq4;
     if (idx >= nrot + (kd >> 2)) return;
-    const RowInfo ri = rows[r];
-    const DocInfo dc = docs[ri.doc];
     // columns c..c+3 of this row, the split-K partial tiles summed in order
     auto load4 = [&](int c) {
         float4 v = *reinterpret_cast<const float4 *>(qkv + (size_t)r * N + c);
@@ -422,14 +430,17 @@ __global__ __launch_bounds__(256) void rope_scatter_vec_kernel(const float *qkv,
         }
         return v;
     };
-    T *cache = (T *)dc.cache;
-    const size_t head_stride = (size_t)dc.n_cap * hd;
     if (idx < nrot) {
         const int j = (hq4 & (hq4 - 1)) == 0 ? idx >> __builtin_ctz(hq4) : idx / hq4, i = (idx - j * hq4) * 4;
         const bool isq = j < Hq;
         const int g = j - Hq;
         const int ca = isq ? j * hd + i : qd + g * hd + i;
+        // the partials do not wait for the row's position and document
         float4 a = load4(ca), b = load4(ca + half);
+        const RowInfo ri = rows[r];
+        const DocInfo dc = docs[ri.doc];
+        T *cache = (T *)dc.cache;
+        const size_t head_stride = (size_t)dc.n_cap * hd;
         const T *bias = isq ? bq : bk;
         if (bias) {
             const int bo = (isq ? j : g) * hd + i;
@@ -452,6 +463,10 @@ __global__ __launch_bounds__(256) void rope_scatter_vec_kernel(const float *qkv,
     } else {
         const int c4 = (idx - nrot) * 4;  // column of the value part [0, kd)
         float4 v = load4(qd + kd + c4);
+        const RowInfo ri = rows[r];
+        const DocInfo dc = docs[ri.doc];
+        T *cache = (T *)dc.cache;
+        const size_t head_stride = (size_t)dc.n_cap * hd;
         if (bv) {
             const float4 bb = load4_f32(bv + c4);
             v.x += bb.x; v.y += bb.y; v.z += bb.z; v.w += bb.w;
