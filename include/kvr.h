@@ -318,8 +318,9 @@ kvr_status kvr_select_to_boundary(int32_t n, int32_t edit_start, int32_t edit_en
  * localization diagnostic that needs the oracle cache, not a repair method.
  * Both caches use the layout of kvr_prefill with their own n_cap; positions
  * (host array, copied during the call) must lie in [0, min(src_n_cap,
- * dst_n_cap)) and be strictly ascending.  Enqueued on `stream` as copy
- * kernels that carry the position list as an argument.  Errors: KVR_E_ARG (NULL
+ * dst_n_cap)) and be strictly ascending.  Enqueued on `stream` as one
+ * 2-D copy (consecutive positions) or as copy kernels that carry the position
+ * list as an argument.  Errors: KVR_E_ARG (NULL
  * context or caches, unsorted positions, misaligned caches), KVR_E_RANGE
  * (a position out of range), KVR_E_HIP. */
 kvr_status kvr_transplant(kvr_ctx *ctx, const void *d_src, int32_t src_n_cap, void *d_dst, int32_t dst_n_cap,

@@ -1040,14 +1040,28 @@ kvr_status kvr_transplant(kvr_ctx *c, const void *d_src, int32_t src_n_cap, void
     hipStream_t s = (hipStream_t)stream;
     const size_t row = (size_t)c->d.head_dim * elem_size(c->d);
     const int planes = c->d.n_layers * 2 * c->d.n_kv_heads;
-    // one launch per COPY_SEGMENTS runs of consecutive positions (a 2-D copy
-    // per run took 2.4 us each: 463 runs in 32 layers, 1297 -> 40 us a call,
-    // 138 MB read and written at 4.5 TB/s)
+    // One run of consecutive positions is one 2-D copy (us a call, 32 layers
+    // of 8 heads, copy against kernel: 1 row 5.6/7.4, 48 rows 7.2/8.6, 4900
+    // rows 273/282).  Several take the kernel, one launch per COPY_SEGMENTS
+    // segments: a 2-D copy per run cost 2.4 us (463 runs 1161 -> 33 us a call,
+    // 138 MB read and written; 528 random rows 1245 -> 27 us).
+    if (h_positions[n_positions - 1] - h_positions[0] == n_positions - 1) {
+        const size_t p0 = (size_t)h_positions[0] * row;
+        const hipError_t e =
+            hipMemcpy2DAsync((char *)d_dst + p0, (size_t)dst_n_cap * row, (const char *)d_src + p0,
+                             (size_t)src_n_cap * row, (size_t)n_positions * row, planes, hipMemcpyDeviceToDevice, s);
+        return e == hipSuccess ? KVR_OK : hip_fail(c, e, "kvr_transplant: hipMemcpy2DAsync");
+    }
+    // A segment's rows are copied one after the other, so a short list is cut
+    // into rows of its own and a long one into as many rows as let it fit one
+    // launch (48 consecutive rows in 16-row segments 11.6 us, in single rows
+    // 8.6; 463 runs 40 and 33 us).
+    const int len = std::min(COPY_LEN, (n_positions + COPY_SEGMENTS - 1) / COPY_SEGMENTS);
     CopySegments sg;
     sg.n = 0;
     for (int i = 0; i < n_positions;) {
         int j = i + 1;
-        while (j < n_positions && j - i < COPY_LEN && h_positions[j] == h_positions[j - 1] + 1) ++j;
+        while (j < n_positions && j - i < len && h_positions[j] == h_positions[j - 1] + 1) ++j;
         sg.start[sg.n] = h_positions[i];
         sg.len[sg.n++] = (uint8_t)(j - i);
         i = j;
