@@ -20,7 +20,8 @@
 // stage it).  Every iteration issues its stage's copies, multiplies, and
 // refills the weight slot it used, in that order and always the same count
 // (k-steps past the slice re-read its last one), so "the loads of the last
-// D - 1 iterations may be in flight" is an exact wait that covers both.  The
+// D - 1 iterations may be in flight" is an exact wait that covers both (a
+// slice of a single k-step issues fewer; its copies are still the oldest).  The
 // barrier is a bare s_barrier: the compiler's workgroup fence would also wait
 // for the loads still in flight.  Registers and LDS leave room for two blocks
 // per compute unit, so that one block's MFMAs run while the other waits; a
@@ -162,10 +163,14 @@ __global__ __launch_bounds__(256, blocks_per_cu(MT)) void linear_tiled_kernel(Li
 #pragma unroll
         for (int j = 0; j < NTW; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // stage 0's copies are the oldest loads: the first wait retires the oldest
+    // FX + NTW, so the scheduler must not hoist weight loads in front of them
 #pragma unroll
     for (int b = 0; b < D; ++b) {
         issue_x(b, b + 1 < nk);
+        __builtin_amdgcn_sched_barrier(0);
         load_w(b, b + 1 < nk);
+        __builtin_amdgcn_sched_barrier(0);
     }
     int rd = 0, wr = D;  // ring stages of k-step kk and of k-step kk + D
     auto step = [&](int b, int kk) {
