@@ -13,8 +13,12 @@
 // bf16 pair hi + lo, so two MFMAs per k-step), so that each lane
 // owns one query row: the row max and sum of a tile are 16 in-lane values plus
 // two cross-lane steps.  The probabilities go straight from the S^T
-// accumulator into the B operand of O^T += V^T P^T (as a compensated pair, two
-// MFMAs per k-step): both operands enumerate the
+// accumulator into the B operand of O^T += V^T P^T, as bf16 pieces with an
+// MFMA each: a compensated pair at HD = 128, three pieces at HD = 64, which
+// hold all 24 bits (with a pair there an output that is 2^-12 of its terms was
+// off by 3.0e-2, with three pieces by 2.2e-3, in fp32 products by 3.8e-3;
+// heads of 64, 1237-token prefill and repair, two layers: 906 -> 923 us).
+// Both operands enumerate the
 // 32 keys of a k-step in the same permuted order (slot j of lane group g <->
 // key 16*(j/4) + 4*g + j%4), so P never leaves registers.  V is staged in LDS
 // in its own [key][dim] layout (16-byte stores) and the V^T operand is read
@@ -90,6 +94,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
                                                                     int o_perm, float *lse) {
     constexpr int KSTEPS = HD / 32, DTILES = HD / 16;  // k-steps of a score, 16-wide dimension tiles
     constexpr int CPR = HD / 8;                        // 16-byte chunks per cache row
+    constexpr int NP = HD == 64 ? 3 : 2;               // bf16 pieces of a probability (head of file)
     constexpr int NLD = KT * CPR / (64 * WAVES);       // 16-byte K (and V) loads per thread per tile
     static_assert(HD % 32 == 0 && NLD * 64 * WAVES == KT * CPR, "tile loads");
     // key tile row stride (bf16): rows 4 banks apart (64-wide heads: 36), so
@@ -218,7 +223,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
                 }
         }
         // online softmax, one query row per lane column
-        bf16x8 pb[PPW][2], pl[PPW][2];
+        bf16x8 pb[PPW][NP][2];  // [..][i]: the i-th bf16 piece of the probabilities
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
             if (!pvalid[i]) continue;
@@ -262,16 +267,19 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
             // B operand P^T for 32-key step ks: slot j <-> key 32*ks + 16*(j/4) + 4*g + j%4
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                u32x4 u, v;
+                u32x4 u[NP];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x2 f = {s[i][2 * ks + q / 2][2 * (q % 2)], s[i][2 * ks + q / 2][2 * (q % 2) + 1]};
-                    const bf16x2 h = __builtin_convertvector(f, bf16x2);
-                    u[q] = __builtin_bit_cast(unsigned int, h);
-                    v[q] = __builtin_bit_cast(unsigned int, __builtin_convertvector(f - __builtin_convertvector(h, f32x2), bf16x2));
+                    f32x2 f = {s[i][2 * ks + q / 2][2 * (q % 2)], s[i][2 * ks + q / 2][2 * (q % 2) + 1]};
+#pragma unroll
+                    for (int x = 0; x < NP; ++x) {
+                        const bf16x2 h = __builtin_convertvector(f, bf16x2);
+                        u[x][q] = __builtin_bit_cast(unsigned int, h);
+                        f -= __builtin_convertvector(h, f32x2);
+                    }
                 }
-                pb[i][ks] = __builtin_bit_cast(bf16x8, u);
-                pl[i][ks] = __builtin_bit_cast(bf16x8, v);
+#pragma unroll
+                for (int x = 0; x < NP; ++x) pb[i][x][ks] = __builtin_bit_cast(bf16x8, u[x]);
             }
         }
         // O^T += V^T P^T: A operand = V^T rows (dims 16*nt + lane%16) over the
@@ -301,13 +309,11 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
                 for (int i = 0; i < PPW; ++i) {
                     if (!pvalid[i]) continue;
 #pragma unroll
-                    for (int nt = 0; nt < NVH; ++nt)
-                        oacc[i][n0 + nt] =
-                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[nt][ks], pb[i][ks], oacc[i][n0 + nt], 0, 0, 0);
+                    for (int x = 0; x < NP; ++x)
 #pragma unroll
-                    for (int nt = 0; nt < NVH; ++nt)
-                        oacc[i][n0 + nt] =
-                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[nt][ks], pl[i][ks], oacc[i][n0 + nt], 0, 0, 0);
+                        for (int nt = 0; nt < NVH; ++nt)
+                            oacc[i][n0 + nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[nt][ks], pb[i][x][ks],
+                                                                                        oacc[i][n0 + nt], 0, 0, 0);
                 }
         }
     }

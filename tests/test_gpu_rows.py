@@ -1,0 +1,71 @@
+"""What a repaired row may depend on, and with how many bits: the attention of
+64-wide heads carries its probabilities in full, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_17983_amd as kvr
+import synth
+from oracle import decoder as od
+from tests.gpu_util import Engine, OracleWeights, relmax, say, to_device_weights
+
+pytestmark = pytest.mark.gpu
+F32, BF16 = kvr.KVR_F32, kvr.KVR_BF16
+
+
+def bf16(x):
+    return torch.as_tensor(np.asarray(x, dtype=np.float64)).to(torch.bfloat16).to(torch.float64).numpy()
+
+
+@pytest.mark.parametrize("items", ["split", "unsplit"])
+def test_probabilities_keep_all_bits(monkeypatch, items):
+    """One row over 200 stale keys whose value rows nearly cancel, so that the roundings of the probabilities and of
+    the sums show some thousand times as large in the output.
+
+    The query is exact (one non-zero dimension whose rotary angle is zero to fp32, embeddings of +-1 and no epsilon), the
+    scores are exact bf16 numbers, the output projection is the identity and the MLP is zero, so that what differs from
+    the oracle is the softmax and P V.  The same sums in numpy: fp32 probabilities added up one by one in fp32 are off by
+    2.9e-3 of the largest output, probabilities rounded to 16 bits (a pair of bf16) and summed exactly by 5.9e-2."""
+    monkeypatch.setenv("KVR_ATT_TARGET", "100000" if items == "split" else "1")
+    hd, hq, hkv, n = 64, 4, 2, 201
+    d = hq * hd
+    shape = synth.ModelShape("exact query", 1, d, hq, hkv, hd, 64, 16, 0.0, 1e30)
+    rng = np.random.default_rng(5)
+    zeros = lambda *s: torch.zeros(s, dtype=torch.bfloat16)
+    wq = zeros(hq * hd, d)
+    wq[31::hd, 0] = 8.0  # q = 8 in dimension 31 of every head: score = key's dimension 31
+    lw = dict(attn_norm=torch.ones(d, dtype=torch.bfloat16), wq=wq, wk=zeros(hkv * hd, d), wv=zeros(hkv * hd, d), bq=None,
+              bk=None, bv=None, wo=torch.eye(d, dtype=torch.bfloat16), mlp_norm=torch.ones(d, dtype=torch.bfloat16),
+              w_gate=zeros(64, d), w_up=zeros(64, d), w_down=zeros(d, 64))
+    embed = torch.from_numpy(rng.choice([-1.0, 1.0], size=(16, d))).to(torch.bfloat16)
+    embed[:, 0] = 1.0
+    w = dict(embed=embed, final_norm=torch.ones(d, dtype=torch.bfloat16), layers=[lw])
+
+    cache = np.zeros((1, 2, hkv, n, hd))
+    score = bf16(rng.uniform(-3, 3, size=(hkv, n - 1)))
+    score[:, 5], score[:, 9] = 3.0, 2.0
+    p = np.exp(score)
+    v = bf16(rng.uniform(-1, 1, size=(hkv, n - 1, hd)) * 2**18)
+    for g in range(hkv):  # two rows take the sum to about 2^-12 of what it was
+        v[g, [5, 9]] = 0
+        v[g, 5] = bf16(-(p[g] @ v[g]) / p[g, 5])
+        left = -(p[g] @ v[g]) / p[g, 9]
+        v[g, 9] = np.ldexp(np.rint(np.ldexp(left, 4 - np.frexp(left)[1])), np.frexp(left)[1] - 4)  # four bits of it
+    cache[0, 0, :, : n - 1, 31] = score
+    cache[0, 1, :, : n - 1] = v
+    assert np.array_equal(bf16(cache), cache)
+
+    tokens = torch.arange(n, dtype=torch.int32) % 16
+    eng = Engine(shape, to_device_weights(w), BF16, max_ctx=n, max_rows=64)
+    try:
+        dev = torch.from_numpy(cache).to(torch.bfloat16).cuda()
+        out = torch.zeros((1, d), device="cuda")
+        say(f"case: cancelling values, {items}")
+        eng.repair([dict(cache=dev, tokens=tokens.cuda(), edit_start=n - 1, edit_end=n, positions=[], hidden=out)])
+        torch.cuda.synchronize()
+        y = od.repair(shape, OracleWeights(w), cache, tokens.numpy(), n - 1, n, [])
+        e = relmax(out.cpu().numpy(), y)
+        say(f"  largest error {e:.2e} of {np.abs(y).max():.2f}")
+        assert e <= 1e-2
+    finally:
+        eng.close()
