@@ -28,7 +28,13 @@
 // per load.  Softmax runs in the exp2 domain; the running max is only
 // raised (and the accumulators rescaled) when a row's tile max exceeds it by
 // more than 2^8, which keeps every probability below 256.  The causal mask is
-// applied only on tiles that reach a row's own position.  The next K/V tile is
+// applied only on tiles that reach a row's own position.  A masked key's
+// probability is zero, but zero times a value that is not finite is not: at
+// HD = 64 the tiles with a mask are searched for such values, which are staged
+// as zeros and added afterwards for the rows that see them (923 -> 927 us for
+// the prefill and repair above).  At HD = 128, where the search cost a
+// scattered repair of a large model 1 %, an infinite or NaN value row reaches
+// every row of the items whose key range holds it.  The next K/V tile is
 // fetched into registers while the current one is used.  The output is written
 // as a compensated pair.  When the key range of a row block is split over
 // several items (few rows, long contexts) each item writes (m, l, unnormalised
@@ -84,6 +90,16 @@ __device__ __forceinline__ float xsum4(float v) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// The bf16 values of u with those that are not finite replaced by zero.
+__device__ __forceinline__ u32x4 finite_or_zero(u32x4 u) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if ((u[e] & 0x7f80u) == 0x7f80u) u[e] &= 0xffff0000u;
+        if ((u[e] & 0x7f800000u) == 0x7f800000u) u[e] &= 0xffffu;
+    }
+    return u;
+}
+
 // HD: head_dim; PPW: (head, row tile) pairs per wavefront; MT: row tiles of a
 // full item.
 template <int HD, int PPW, int KG>
@@ -95,6 +111,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
     constexpr int KSTEPS = HD / 32, DTILES = HD / 16;  // k-steps of a score, 16-wide dimension tiles
     constexpr int CPR = HD / 8;                        // 16-byte chunks per cache row
     constexpr int NP = HD == 64 ? 3 : 2;               // bf16 pieces of a probability (head of file)
+    constexpr bool MASKED_EXACT = HD == 64;
     constexpr int NLD = KT * CPR / (64 * WAVES);       // 16-byte K (and V) loads per thread per tile
     static_assert(HD % 32 == 0 && NLD * 64 * WAVES == KT * CPR, "tile loads");
     // key tile row stride (bf16): rows 4 banks apart (64-wide heads: 36), so
@@ -107,6 +124,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
     // loop the same memory takes the second key group's softmax state
     __shared__ __attribute__((aligned(16))) bf16_t kv_lds[KG * KT * (KS_STRIDE + VS_STRIDE)];
     bf16_t *Ks = kv_lds, *Vs = kv_lds + KG * KT * KS_STRIDE;
+    __shared__ int bad_tile;  // first key of the last staged tiles that hold a value that is not finite
 
     const AttnItem it = items[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4;
@@ -166,6 +184,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
         }                                                                                                   \
     }
     KVR_ATT_FETCH(it.k0)
+    if (MASKED_EXACT && tid == 0) bad_tile = -1;
     for (int kb0 = it.k0; kb0 < it.k1; kb0 += KG * KT) {
         __syncthreads();
 #pragma clang loop unroll(full)
@@ -177,6 +196,26 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
                 *reinterpret_cast<u32x4 *>(&Vs[key * VS_STRIDE + (tid % CPR) * 8]) = vreg[q][i];
             }
         }
+        if (MASKED_EXACT && !(kb0 + KG * KT <= it.k1 && kb0 + KG * KT - 1 <= minpos)) {
+            // an exponent of all ones carries into the bit above it
+            unsigned int t = 0;
+#pragma unroll
+            for (int q = 0; q < KG; ++q)
+#pragma unroll
+                for (int i = 0; i < NLD; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t |= (vreg[q][i][e] & 0x7f807f80u) + 0x00800080u;
+            if (t & 0x80008000u) {
+                bad_tile = kb0;
+#pragma clang loop unroll(full)
+                for (int q = 0; q < KG; ++q)
+#pragma clang loop unroll(full)
+                    for (int i = 0; i < NLD; ++i) {
+                        const int key = q * KT + (tid + 64 * WAVES * i) / CPR;
+                        *reinterpret_cast<u32x4 *>(&Vs[key * VS_STRIDE + (tid % CPR) * 8]) = finite_or_zero(vreg[q][i]);
+                    }
+            }
+        }
         __syncthreads();
         if (kb0 + KG * KT < it.k1) {
             KVR_ATT_FETCH(kb0 + KG * KT)
@@ -185,6 +224,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
         if (kt >= it.k1) continue;
         const bf16_t *Kt = Ks + kg * KT * KS_STRIDE, *Vt = Vs + kg * KT * VS_STRIDE;
         const bool full = kt + KT <= it.k1 && kt + KT - 1 <= minpos;  // no key of the tile is masked
+        const bool bad = MASKED_EXACT && !full && bad_tile == kb0;
 
         // S^T = K Q^T: lane holds query row lane%16, keys 16*nt + 4*g + e of the
         // tile.  The key fragments are read from LDS first, then the MFMAs run
@@ -315,6 +355,26 @@ __global__ __launch_bounds__(64 * WAVES) void attention_mfma_kernel(const bf16_t
                             oacc[i][n0 + nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[nt][ks], pb[i][x][ks],
                                                                                         oacc[i][n0 + nt], 0, 0, 0);
                 }
+        }
+        if (bad) {  // the values left out of the product, for the rows that see their keys
+            const int nk = min(KT, it.k1 - kt);
+#pragma unroll 1
+            for (int k = 0; k < nk; ++k) {
+                const bf16_t *vr = Vg + (size_t)(kt + k) * HD + 4 * g;
+#pragma unroll
+                for (int nt = 0; nt < DTILES; ++nt) {
+                    const uint2 u = *reinterpret_cast<const uint2 *>(vr + nt * 16);
+                    if (!((((u.x & 0x7f807f80u) + 0x00800080u) | ((u.y & 0x7f807f80u) + 0x00800080u)) & 0x80008000u))
+                        continue;
+                    const float v[4] = {__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
+                                        __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
+#pragma unroll
+                    for (int i = 0; i < PPW; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (!isfinite(v[e]) && kt + k <= prow[i]) oacc[i][nt][e] += v[e];
+                }
+            }
         }
     }
 #undef KVR_ATT_FETCH

@@ -21,6 +21,11 @@
 // per item the wavefronts split into KG key groups that take alternate 16-key
 // tiles and merge their softmax states in LDS at the end.
 //
+// A row depends on no slot behind its position, whatever that slot holds: in
+// the tiles that have a mask, values that are not finite are staged as zeros
+// (a masked key's probability is zero, its product with them would not be) and
+// added afterwards for the rows that see them.
+//
 // What bounds it: the fp32 matrix rate on long contexts (16 instructions of
 // 32 cycles per 16 keys x 16 rows at head_dim 64), latency on short ones.
 // Tiny fp32 decoder (4 heads of 64), per layer against the kernel it replaced
@@ -95,6 +100,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_generic_kernel(const T *
     constexpr int PART_ROW = HDP + 4;
     __shared__ __attribute__((aligned(16))) float kv_lds[2 * KT * LD];
     float *Ks = kv_lds, *Vs = kv_lds + KT * LD;
+    __shared__ int bad_tile;  // first key of the last staged tile that holds a value that is not finite
 
     const AttnItem it = items[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4;
@@ -108,6 +114,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_generic_kernel(const T *
     const int ri = pm * 16 + (lane & 15);              // this lane's query row within the item
     const int pos = (pvalid && ri < it.nrows) ? rows[it.row0 + ri].pos : -1;
     const int j = it.kvh * G + pt;
+    const int minpos = rows[it.row0].pos;              // rows ascend: every row sees all keys <= minpos
     const bool vec = (hd & 3) == 0;
     const size_t head_stride = (size_t)it.n_cap * hd;
     const T *Kg = (const T *)it.cache + (((size_t)layer * 2 + 0) * Hkv + it.kvh) * head_stride;
@@ -140,6 +147,7 @@ __global__ __launch_bounds__(64 * WAVES) void attention_generic_kernel(const T *
         }
     };
     fetch(it.k0);
+    if (tid == 0) bad_tile = -1;
     for (int kb = it.k0; kb < it.k1; kb += KT) {
         __syncthreads();
 #pragma unroll
@@ -147,6 +155,27 @@ __global__ __launch_bounds__(64 * WAVES) void attention_generic_kernel(const T *
             const int c = tid + 64 * WAVES * i;
             *reinterpret_cast<f32x4 *>(&Ks[(c / CPR) * LD + 4 * (c % CPR)]) = kreg[i];
             *reinterpret_cast<f32x4 *>(&Vs[(c / CPR) * LD + 4 * (c % CPR)]) = vreg[i];
+        }
+        const bool masked = kb + KT > it.k1 || kb + KT - 1 > minpos;
+        if (masked) {
+            // A masked key's probability is zero, and so is its product unless
+            // its value is not finite: those are left out here and added below
+            // for the rows that see them.
+            float t = 0.f;
+#pragma unroll
+            for (int i = 0; i < NLD; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t = fmaf(vreg[i][e], 0.f, t);
+            if (t != 0.f) {
+                bad_tile = kb;
+#pragma unroll
+                for (int i = 0; i < NLD; ++i) {
+                    const int c = tid + 64 * WAVES * i;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (!isfinite(vreg[i][e])) Vs[(c / CPR) * LD + 4 * (c % CPR) + e] = 0.f;
+                }
+            }
         }
         __syncthreads();
         if (kb + KT < it.k1) fetch(kb + KT);
@@ -196,6 +225,20 @@ __global__ __launch_bounds__(64 * WAVES) void attention_generic_kernel(const T *
                 for (int q = 0; q < DQ; ++q)
                     oacc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[16 * q], pr, oacc[q], 0, 0, 0);
             }
+        if (masked && bad_tile == kb) {
+            const int nk = min(KT, it.k1 - kb);
+#pragma unroll 1
+            for (int k = 0; k < nk; ++k) {
+                if ((k >> 4) % KG != kg) continue;
+#pragma unroll
+                for (int q = 0; q < DQ; ++q) {
+                    const f32x4 v = load_dims(Vg + (size_t)(kb + k) * hd, 16 * q + 4 * g, hd, vec);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (!isfinite(v[e]) && kb + k <= pos) oacc[q][e] += v[e];
+                }
+            }
+        }
     }
     l = xsum4(l);
 

@@ -1,5 +1,5 @@
 """What a repaired row may depend on, and with how many bits: the attention of
-64-wide heads carries its probabilities in full, against the fp64 oracle."""
+64-wide heads carries its probabilities in full, and no row sees a later slot."""
 import numpy as np
 import pytest
 import torch
@@ -7,7 +7,7 @@ import torch
 import paper_2609_17983_amd as kvr
 import synth
 from oracle import decoder as od
-from tests.gpu_util import Engine, OracleWeights, relmax, say, to_device_weights
+from tests.gpu_util import TOL, Engine, OracleWeights, relmax, say, to_device_weights
 
 pytestmark = pytest.mark.gpu
 F32, BF16 = kvr.KVR_F32, kvr.KVR_BF16
@@ -67,5 +67,50 @@ def test_probabilities_keep_all_bits(monkeypatch, items):
         e = relmax(out.cpu().numpy(), y)
         say(f"  largest error {e:.2e} of {np.abs(y).max():.2f}")
         assert e <= 1e-2
+    finally:
+        eng.close()
+
+
+# bf16 heads of 64 (two key groups, one and two pairs per wavefront), the generic kernel in both types, both paddings,
+# head widths that are not multiples of four, and one, two and four wavefronts per pair
+POISON = [(BF16, 64, 4, 4), (BF16, 64, 8, 2), (BF16, 64, 14, 2), (BF16, 80, 4, 2), (BF16, 18, 4, 2), (F32, 64, 4, 4),
+          (F32, 64, 4, 2), (F32, 64, 8, 2), (F32, 128, 4, 4), (F32, 6, 6, 2), (F32, 96, 4, 1)]
+
+
+@pytest.mark.parametrize("items", ["split", "unsplit"])
+@pytest.mark.parametrize("dtype,hd,hq,hkv", POISON, ids=[f"{'bf16' if t else 'f32'}-{d}x{a}/{b}" for t, d, a, b in POISON])
+def test_rows_do_not_see_later_slots(monkeypatch, dtype, hd, hq, hkv, items):
+    """Slots of the stale cache hold infinities and NaN: the rows before them, in the same row tile as rows behind them,
+    are what they are without, and the rows behind them show it."""
+    monkeypatch.setenv("KVR_ATT_TARGET", "100000" if items == "split" else "1")
+    shape = synth.ModelShape(f"poison {hd}x{hq}/{hkv} {items}", 2, 64, hq, hkv, hd, 64, 128, 1e-5, 10000.0)
+    n, bad = 400, 170
+    tdt = torch.bfloat16 if dtype == BF16 else torch.float32
+    w = synth.make_weights(shape, dtype=tdt, seed=hd)
+    A = [3, 90, 150, 169, 172, 230, 231, 232, 399]
+    P = np.asarray(od.repaired_set(100, 104, A))
+    before = P < bad
+    clean = synth.make_stale_cache(shape, n).to(tdt)
+    stale = clean.clone()
+    stale[:, 0, :, bad, hd - 1] = float("nan")
+    stale[:, 1, 0, bad, 0] = float("inf")
+    stale[:, 1, :, bad + 1, hd // 2] = float("nan")
+    stale[:, 1, :, n - 2, 1] = -float("inf")
+    toks = synth.make_tokens(n, shape.vocab, seed=1)
+    eng = Engine(shape, to_device_weights(w), dtype, max_ctx=n, max_rows=64)
+    try:
+        dev, out = stale.cuda(), torch.zeros((len(P), shape.d_model), device="cuda")
+        say(f"case: {shape.name}")
+        eng.repair([dict(cache=dev, tokens=toks.cuda(), edit_start=100, edit_end=104, positions=A, hidden=out)])
+        torch.cuda.synchronize()
+        ref = clean.to(torch.float64).numpy()
+        y = od.repair(shape, OracleWeights(w), ref, toks.numpy(), 100, 104, A)
+        got, after = out.cpu().numpy(), dev.to(torch.float64).cpu().numpy()
+        assert np.isfinite(got[before]).all() and not np.isfinite(got[~before]).all(axis=1).any()
+        assert relmax(got[before], y[before]) <= TOL[dtype]
+        for l in range(2):
+            for kv in range(2):
+                rows = P[before]
+                assert relmax(after[l, kv][:, rows], ref[l, kv][:, rows]) <= TOL[dtype]
     finally:
         eng.close()
