@@ -132,6 +132,7 @@ struct LinearArgs {
     int32_t ldo;
     int32_t split;        // STORE only: K cut into `split` slices, partial
                           // tiles out[s][R][ldo] summed by the consumer (<= 1: none)
+    int32_t kslices;      // generic STORE only: K slices of the sum (<= 1: one); split is this or 1
     int32_t group_all;    // tiled: at most this many row blocks form one group of the tile order (set by the launcher)
     int32_t rt;           // tiled kernel: 16-row tiles per block
     int32_t tpb;          // tall kernel: weight tiles per block (0: not the tall kernel)
@@ -204,16 +205,18 @@ hipError_t launch_embed(bool bf16, const EmbedArgs &args, const void *embed, con
 // RMSNorm of the residual rows.  First H[r] += sum of `nsplit` fp32 partial
 // tiles part[s][R][d] (the split-K outputs of the projection that produced the
 // residual update; nsplit 0 = none), then X = H * rsqrt(mean(H^2)+eps) * gain,
-// row-major with stride ldx, or in operand order when `perm`.
-hipError_t launch_rmsnorm(bool bf16, float *H, const float *part, int nsplit, const void *gain, int R, int d, float eps,
-                          void *X, void *X_lo, int ldx, bool perm, hipStream_t s);
+// row-major with stride ldx, or in operand order when `perm`.  The tiles are
+// added to H one by one or, with sum_first, to each other and then to H, which
+// is what one tile that holds their sum gives (generic projections).
+hipError_t launch_rmsnorm(bool bf16, float *H, const float *part, int nsplit, bool sum_first, const void *gain, int R, int d,
+                          float eps, void *X, void *X_lo, int ldx, bool perm, hipStream_t s);
 // Residual update + gain for the skinny path (see resid_gain_kernel): H[r] +=
 // partials, X = H * gain (compensated, operand order), ssq[b][r] per 1024-column
 // block b; resid_gain_blocks(d) blocks per row.
 int resid_gain_blocks(int d);
 hipError_t launch_resid_gain(bool bf16_gain, float *H, const float *part, int nsplit, const void *gain, int R, int d,
                              void *X, void *X_lo, float *ssq, hipStream_t s);
-hipError_t launch_final_norm(bool bf16_gain, float *H, const float *part, int nsplit, const void *gain,
+hipError_t launch_final_norm(bool bf16_gain, float *H, const float *part, int nsplit, bool sum_first, const void *gain,
                              const RowInfo *rows, const DocInfo *docs, int R, int d, float eps, hipStream_t s);
 // qkv: `nsplit` fp32 tiles [nsplit][R][qd+2kd] summed in order.
 hipError_t launch_rope_scatter(bool bf16, const float *qkv, int nsplit, const void *bq, const void *bk,
@@ -243,10 +246,13 @@ hipError_t launch_attention_mfma(const bf16_t *Q, const bf16_t *Q_lo, const RowI
                                  float *part, bf16_t *O, bf16_t *O_lo, bool o_perm, float *lse, hipStream_t s);
 hipError_t launch_attention_combine(bool bf16, const CombineItem *items, int n_items, int MT, const float *part, int Hq,
                                     int Hkv, int hd, void *O, void *O_lo, bool o_perm, float *lse, hipStream_t s);
-// Any R, N, K, fp32 or bf16, row-major operands (a.w); a.split K slices of a
-// STORE launch go to partial tiles out[s][R][ldo] (generic_split picks them).
+// Any R, N, K, fp32 or bf16, row-major operands (a.w).  A STORE output is the
+// sum of a.kslices K slices in order (generic_slices), added up in the kernel
+// (a.split 1) or left as partial tiles out[s][R][ldo] (a.split == a.kslices;
+// always up to 64 rows); generic_split picks which.
 hipError_t launch_linear_generic(bool bf16, int epi, const LinearArgs &a, hipStream_t s);
-int generic_split(int R, int N, int K, size_t part_floats);
+int generic_slices(int N, int K);
+int generic_split(int R, int N, int slices, size_t part_floats);
 // Skinny MFMA path (R <= 64); nt = 16-row weight tiles per block (1..8).
 hipError_t launch_linear_skinny(int epi, const SkinnyArgs &a, int nt, hipStream_t s);
 // Tiled MFMA path for many rows (packed weight, K a multiple of 32,

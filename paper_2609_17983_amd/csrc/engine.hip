@@ -400,8 +400,12 @@ void plan_linear(const kvr_ctx *c, LinearArgs &a, int epi) {
     const int vrows = epi == EPI_SWIGLU ? 2 * a.N : a.N;
     a.tpb = 0;
     a.split = 1;
+    a.kslices = 1;
     if (!a.wp) {
-        if (epi == EPI_STORE) a.split = generic_split(a.R, a.N, a.K, c->p_floats);
+        if (epi == EPI_STORE) {
+            a.kslices = generic_slices(a.N, a.K);
+            a.split = generic_split(a.R, a.N, a.kslices, c->p_floats);
+        }
         return;
     }
     if (tall_rows_ok(a.R) && env_int("KVR_TALL", 1) != 0) {
@@ -597,8 +601,8 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
             KVR_CHECK(launch_resid_gain(bf, c->H, c->P, resid_split, w.attn_norm, R, D, c->Xn, c->Xn_lo, c->rs_ssq, s),
                       "rmsnorm(attn)", ST_NORM);
         else
-            KVR_CHECK(launch_rmsnorm(bf, c->H, c->P, resid_split, w.attn_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo, D,
-                                     op, s),
+            KVR_CHECK(launch_rmsnorm(bf, c->H, c->P, resid_split, !op, w.attn_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo,
+                                     D, op, s),
                       "rmsnorm(attn)", ST_NORM);
         int qkv_split = 1;
         if (sk) {
@@ -657,8 +661,8 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
             KVR_CHECK(launch_resid_gain(bf, c->H, c->P, resid_split, w.mlp_norm, R, D, c->Xn, c->Xn_lo, c->rs_ssq, s),
                       "rmsnorm(mlp)", ST_NORM);
         else
-            KVR_CHECK(launch_rmsnorm(bf, c->H, c->P, resid_split, w.mlp_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo, D, op,
-                                     s),
+            KVR_CHECK(launch_rmsnorm(bf, c->H, c->P, resid_split, !op, w.mlp_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo,
+                                     D, op, s),
                       "rmsnorm(mlp)", ST_NORM);
         resid_split = 0;
         if (sk) {
@@ -695,10 +699,10 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
         }
     }
     if (lm_operand)
-        KVR_CHECK(launch_rmsnorm(bf, c->H, c->P, resid_split, c->final_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo, D,
+        KVR_CHECK(launch_rmsnorm(bf, c->H, c->P, resid_split, !op, c->final_norm, R, D, d.rms_eps, c->Xn, c->Xn_lo, D,
                                  c->lm_pk != nullptr, s), "final_norm", ST_FINAL);
     else
-        KVR_CHECK(launch_final_norm(bf, c->H, c->P, resid_split, c->final_norm, rows, docs, R, D, d.rms_eps, s),
+        KVR_CHECK(launch_final_norm(bf, c->H, c->P, resid_split, !op, c->final_norm, rows, docs, R, D, d.rms_eps, s),
                   "final_norm", ST_FINAL);
 #undef KVR_CHECK
     return KVR_OK;

@@ -19,8 +19,18 @@
 // wavefront tiles straight from memory was bound by the bytes a compute unit
 // takes in (16 rows x 64 bytes per load: Q/K/V of
 // 1501 rows 21 us, where the LDS tile takes 13).
-// A STORE launch may also be cut into `split` K slices (grid z) whose fp32
-// partial tiles the next row kernel sums in order.
+//
+// One K order for every row count.  K is cut into kslices slices of four
+// quarters (part_start: at 32-wide k-steps, by K and the slice count alone,
+// which generic_slices takes from N and K).  A quarter is one chain of
+// products, a slice the sum of its quarters in order, an output the sum of its
+// slices in order.  Up to 64 rows, a quarter is a wavefront and a slice a
+// block (grid z) whose fp32 partial tile the next row kernel sums in slice
+// order; the tiled kernel walks the same quarters and adds them up alike,
+// either one slice per block or all of them (split 1).  A row's result
+// therefore does not depend on the rows it shares a pass with: equal tokens at
+// equal positions have bit-equal keys and values at layer 0, whether a prefill
+// or a suffix computed them (CacheBlend's deviations there are exactly zero).
 //
 // What bounds it: latency for a few rows (a 256 x 256 projection of 40 rows is
 // four steps per wavefront), the fp32 matrix rate and the fill of the chip for
@@ -65,6 +75,9 @@ __device__ __forceinline__ f32x4 load_tail(const T *p, int left) {
     return v;
 }
 
+// First 32-wide k-step of part i of `parts` (quarters of a slice).
+__device__ __forceinline__ int part_start(int steps, int i, int parts) { return steps * i / parts; }
+
 // Row-major weight row of output column n (SwiGLU: part 0 gate, 1 up).
 template <typename T, int EPI>
 __device__ __forceinline__ const T *weight_row(const LinearArgs &a, int n, int part) {
@@ -74,17 +87,19 @@ __device__ __forceinline__ const T *weight_row(const LinearArgs &a, int n, int p
 }
 
 // Rows r0 + 16 m + 4 (lane/16) + e, column n of an accumulator tile (the layout:
-// lane l holds tile column l%16).
+// lane l holds tile column l%16); add: to what this thread stored there before.
 template <typename T, int EPI>
-__device__ __forceinline__ void store_tile(const LinearArgs &a, int r, int n, f32x4 v, f32x4 up) {
+__device__ __forceinline__ void store_tile(const LinearArgs &a, int r, int n, f32x4 v, f32x4 up, bool add = false) {
     if (n >= a.N) return;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         if (r + e >= a.R) continue;
         if (EPI == EPI_SWIGLU)
             store_operand((T *)a.out, (T *)a.out_lo, (size_t)(r + e) * a.ldo + n, silu_f(v[e]) * up[e]);
-        else
-            ((float *)a.out)[((size_t)blockIdx.z * a.R + r + e) * a.ldo + n] = v[e];
+        else {
+            float *o = (float *)a.out + ((size_t)blockIdx.z * a.R + r + e) * a.ldo + n;
+            *o = add ? *o + v[e] : v[e];
+        }
     }
 }
 
@@ -96,9 +111,9 @@ __global__ __launch_bounds__(256) void linear_generic_kernel(LinearArgs a) {
     const int lane = threadIdx.x & 63, g = lane >> 4;
     const int kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c0 = blockIdx.x * 16;
-    const int split = EPI == EPI_STORE && a.split > 1 ? a.split : 1;
-    const int steps = a.K >> 4, part = blockIdx.z * KW + kw, parts = split * KW;
-    const int s0 = steps * part / parts, s1 = steps * (part + 1) / parts;
+    const int steps = a.K >> 4, pairs = (a.K + 31) >> 5;  // whole 16-wide k-steps; 32-wide ones, the last may be shorter
+    const int part = blockIdx.z * KW + kw, parts = gridDim.z * KW;
+    const int s0 = 2 * part_start(pairs, part, parts), s1 = min(steps, 2 * part_start(pairs, part + 1, parts));
 
     // rows and columns past the end re-read the last one; their results are not stored
     const T *xp[MT], *xl[MT], *wp[NT];
@@ -195,7 +210,7 @@ __global__ __launch_bounds__(256) void linear_generic_kernel(LinearArgs a) {
 // WT x WT tiles of 16 x 16 per wavefront; block tile 32 WT x 32 WT (SwiGLU:
 // 16 WT features, each wavefront's first WT / 2 column tiles gate, then up).
 template <typename T, int EPI, int WT, bool VEC>
-__global__ __launch_bounds__(256) void linear_generic_tiled_kernel(LinearArgs a) {
+__global__ __launch_bounds__(256, 2) void linear_generic_tiled_kernel(LinearArgs a) {
     constexpr int B = 32 * WT, KB = 32, LD = KB + 4;
     constexpr int CH = B * KB / 4 / 256;                     // float4 chunks per thread and operand
     constexpr int CT = EPI == EPI_SWIGLU ? WT / 2 : WT;      // output column tiles of a wavefront
@@ -204,18 +219,18 @@ __global__ __launch_bounds__(256) void linear_generic_tiled_kernel(LinearArgs a)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = w >> 1, wn = w & 1;
     const int r0 = blockIdx.y * B, c0 = blockIdx.x * 32 * CT;
-    const int split = EPI == EPI_STORE && a.split > 1 ? a.split : 1;
-    const int steps = (a.K + KB - 1) / KB;
-    const int s0 = steps * (int)blockIdx.z / split, s1 = steps * ((int)blockIdx.z + 1) / split;
+    // this block's quarters [p0, pend) of `parts`
+    const int steps = (a.K + KB - 1) / KB, parts = 4 * (EPI == EPI_STORE ? max(1, a.kslices) : 1);
+    const int p0 = parts / gridDim.z * blockIdx.z, pend = p0 + parts / gridDim.z;
+    const int send = part_start(steps, pend, parts);
 
     // staging: chunk i of this thread is row (tid + 256 i) / 8, k 4 (tid % 8) .. +3
-    const T *xp[CH], *xl[CH], *wp[CH];
+    size_t xo[CH];
+    const T *wp[CH];
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
         const int v = (tid + 256 * i) >> 3;
-        const size_t o = (size_t)min(r0 + v, a.R - 1) * a.ldx;
-        xp[i] = (const T *)a.x + o;
-        xl[i] = (const T *)a.x_lo + o;
+        xo[i] = (size_t)min(r0 + v, a.R - 1) * a.ldx;
         // W row v of the tile: wavefront column v / (16 WT), tile and column within it
         const int t = (v >> 4) % WT;
         const int n = c0 + (v / (16 * WT)) * 16 * CT + (t % CT) * 16 + (v & 15);
@@ -228,56 +243,80 @@ __global__ __launch_bounds__(256) void linear_generic_tiled_kernel(LinearArgs a)
         return load_tail(p + min(k, a.K), a.K - k);
     };
     auto fetch = [&](int s) {
+        const int k = KB * s + kt;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            xr[i] = load(xp[i], KB * s + kt);
-            if constexpr (sizeof(T) == 2) xr[i] += load(xl[i], KB * s + kt);
-            wr[i] = load(wp[i], KB * s + kt);
+            xr[i] = load((const T *)a.x + xo[i], k);
+            if constexpr (sizeof(T) == 2) xr[i] += load((const T *)a.x_lo + xo[i], k);
+            wr[i] = load(wp[i], k);
         }
     };
-    f32x4 acc[WT][WT];
+    // the running quarter, slice and output; the larger tile keeps its output in
+    // memory between slices (a third set of sums in registers would leave one
+    // block per unit)
+    constexpr bool TOT = EPI == EPI_STORE && WT == 2;
+    f32x4 acc[WT][WT], sum[WT][WT], tot[WT][WT];
 #pragma unroll
     for (int m = 0; m < WT; ++m)
 #pragma unroll
-        for (int j = 0; j < WT; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (s0 < s1) fetch(s0);
-    for (int s = s0; s < s1; ++s) {
-        float *st = lds[(s - s0) & 1];
+        for (int j = 0; j < WT; ++j) acc[m][j] = sum[m][j] = tot[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int s = part_start(steps, p0, parts);
+    if (s < send) fetch(s);
+    for (int p = p0; p < pend; ++p) {
+        for (const int e = part_start(steps, p + 1, parts); s < e; ++s) {
+            float *st = lds[s & 1];
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const int o = ((tid + 256 * i) >> 3) * LD + kt;
-            *reinterpret_cast<f32x4 *>(st + o) = xr[i];
-            *reinterpret_cast<f32x4 *>(st + B * LD + o) = wr[i];
-        }
-        // one barrier per step: a stage is written again two steps later, when
-        // every wavefront has passed the barrier after its last read
-        __syncthreads();
-        if (s + 1 < s1) fetch(s + 1);
-        const float *xs = st + (16 * WT * wm + (lane & 15)) * LD + 4 * g;
-        const float *ws = st + (B + 16 * WT * wn + (lane & 15)) * LD + 4 * g;
-#pragma unroll
-        for (int q = 0; q < KB / 16; ++q) {
-            f32x4 xv[WT], wv[WT];
-#pragma unroll
-            for (int m = 0; m < WT; ++m) {
-                xv[m] = *reinterpret_cast<const f32x4 *>(xs + 16 * m * LD + 16 * q);
-                wv[m] = *reinterpret_cast<const f32x4 *>(ws + 16 * m * LD + 16 * q);
+            for (int i = 0; i < CH; ++i) {
+                const int o = ((tid + 256 * i) >> 3) * LD + kt;
+                *reinterpret_cast<f32x4 *>(st + o) = xr[i];
+                *reinterpret_cast<f32x4 *>(st + B * LD + o) = wr[i];
             }
+            // one barrier per step: a stage is written again two steps later, when
+            // every wavefront has passed the barrier after its last read
+            __syncthreads();
+            if (s + 1 < send) fetch(s + 1);
+            const float *xs = st + (16 * WT * wm + (lane & 15)) * LD + 4 * g;
+            const float *ws = st + (B + 16 * WT * wn + (lane & 15)) * LD + 4 * g;
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
+            for (int q = 0; q < KB / 16; ++q) {
+                if (WT == 4) __builtin_amdgcn_sched_barrier(0);  // registers: one half-step's fragments at a time
+                f32x4 xv[WT], wv[WT];
 #pragma unroll
-                for (int m = 0; m < WT; ++m)
+                for (int m = 0; m < WT; ++m) {
+                    xv[m] = *reinterpret_cast<const f32x4 *>(xs + 16 * m * LD + 16 * q);
+                    wv[m] = *reinterpret_cast<const f32x4 *>(ws + 16 * m * LD + 16 * q);
+                }
 #pragma unroll
-                    for (int j = 0; j < WT; ++j)
-                        acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[m][c], wv[j][c], acc[m][j], 0, 0, 0);
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int m = 0; m < WT; ++m)
+#pragma unroll
+                        for (int j = 0; j < WT; ++j)
+                            acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[m][c], wv[j][c], acc[m][j], 0, 0, 0);
+            }
         }
+        const bool end = (p & 3) == 3;  // of a slice
+#pragma unroll
+        for (int m = 0; m < WT; ++m)
+#pragma unroll
+            for (int j = 0; j < WT; ++j) {
+                sum[m][j] += acc[m][j];
+                acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (TOT && end) {
+                    tot[m][j] += sum[m][j];
+                    sum[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+        if (TOT ? p + 1 < pend : !end) continue;
+#pragma unroll
+        for (int m = 0; m < WT; ++m)
+#pragma unroll
+            for (int j = 0; j < CT; ++j) {
+                store_tile<T, EPI>(a, r0 + 16 * (WT * wm + m) + 4 * g, c0 + 16 * (CT * wn + j) + (lane & 15),
+                                   TOT ? tot[m][j] : sum[m][j], sum[m][(j + CT) % WT], !TOT && p > p0 + 3);
+                if (EPI == EPI_STORE) sum[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
     }
-#pragma unroll
-    for (int m = 0; m < WT; ++m)
-#pragma unroll
-        for (int j = 0; j < CT; ++j)
-            store_tile<T, EPI>(a, r0 + 16 * (WT * wm + m) + 4 * g, c0 + 16 * (CT * wn + j) + (lane & 15), acc[m][j],
-                               acc[m][(j + CT) % WT]);
 }
 
 // Output tiles of a tiled launch: 128 x 128 when there are two for every
@@ -288,7 +327,10 @@ int generic_tile(int R, int vcols) {
 
 template <typename T, int EPI, bool VEC>
 hipError_t launch_vec(const LinearArgs &a, hipStream_t s) {
-    const unsigned z = EPI == EPI_STORE ? std::max(1, (int)a.split) : 1;
+    // a row block of up to 64 rows runs a block per slice, a tile one or all
+    const int slices = EPI == EPI_STORE ? std::max(1, (int)a.kslices) : 1;
+    const int z = EPI == EPI_STORE ? std::max(1, (int)a.split) : 1;
+    if (z != slices && (z != 1 || a.R <= 64)) return hipErrorInvalidValue;
     const int vcols = EPI == EPI_SWIGLU ? 2 * a.N : a.N;
     if (a.R <= 64) {
         const dim3 grid((a.N + 15) / 16, 1, z);
@@ -314,15 +356,23 @@ hipError_t launch_epi(const LinearArgs &a, hipStream_t s) {
 
 }  // namespace
 
-// K slices of a STORE launch: up to two blocks per compute unit, at least four
-// k-steps per wavefront (64 k with K split over the wavefronts, 128 k in a
-// tile), and no more partial tiles than fit.
-int generic_split(int R, int N, int K, size_t part_floats) {
-    const int b = R <= 64 ? 0 : 32 * generic_tile(R, N);
-    const long long blocks = b ? (long long)((R + b - 1) / b) * ((N + b - 1) / b) : (N + 15) / 16;
-    long long sp = std::min<long long>(512 / blocks, K / (b ? 128 : 256));
-    sp = std::min<long long>(sp, (long long)(part_floats / ((size_t)R * N)));
-    return (int)std::max<long long>(1, std::min<long long>(sp, 8));
+// K slices of the sum of a STORE launch, whatever its rows: up to two blocks
+// per compute unit for a row block of 64, and slices of 256 k, or of 128 while
+// those are no more than four (tiny fp32 decoder, 600-token prefill: 136 us a
+// call against 152 with slices of 256 only, which leave a 256-wide projection
+// to 40 blocks; its 40-row repair takes 101-104 us either way).
+int generic_slices(int N, int K) {
+    return std::max(1, std::min({512 / ((N + 15) / 16), std::max(std::min(K / 128, 4), K / 256), 8}));
+}
+
+// Partial tiles of a STORE launch (a.split): a block per slice up to 64 rows,
+// and for more while that leaves at most two blocks per compute unit and the
+// partial tiles fit; else a block adds up every slice itself.
+int generic_split(int R, int N, int slices, size_t part_floats) {
+    if (R <= 64) return slices;
+    const int b = 32 * generic_tile(R, N);
+    const long long blocks = (long long)((R + b - 1) / b) * ((N + b - 1) / b);
+    return blocks * 2 <= 512 && (size_t)slices * R * N <= part_floats ? slices : 1;
 }
 
 hipError_t launch_linear_generic(bool bf16, int epi, const LinearArgs &a, hipStream_t s) {

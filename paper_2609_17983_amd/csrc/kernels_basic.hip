@@ -112,13 +112,13 @@ struct HiddenOut {
     int out;
 };
 
-// H[r] += sum of the split-K partial tiles (fixed order), then
-// H * rsqrt(mean(H^2) + eps) * gain to `o`.  One block per row, as many
+// H[r] += sum of the split-K partial tiles (fixed order; sum_first: added to
+// each other before H), then H * rsqrt(mean(H^2) + eps) * gain to `o`.  One block per row, as many
 // wavefronts as the row has 256-column pieces, at most 16; the row stays in
 // registers between the two passes (four columns per thread per pass, d % 4
 // == 0).  After the last layer H is not written back.
 template <typename TG, typename OUT>
-__global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *part, int nsplit, int R,
+__global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *part, int nsplit, bool sum_first, int R,
                                                        const TG *gain, int d, float eps, OUT o) {
     __shared__ float red[16];
     const int r = blockIdx.x;
@@ -133,7 +133,13 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *H, const float *pa
         gn[k] = load_gain4(gain + 4 * i);
         v[k] = *reinterpret_cast<const float4 *>(h + 4 * i);
         if (nsplit) {
-            v[k] = add_partials(v[k], part, nsplit, R, r, d, i);
+            if (sum_first) {
+                float4 p = *reinterpret_cast<const float4 *>(part + (size_t)r * d + 4 * i);
+                p = add_partials(p, part + (size_t)R * d, nsplit - 1, R, r, d, i);
+                v[k].x += p.x; v[k].y += p.y; v[k].z += p.z; v[k].w += p.w;
+            } else {
+                v[k] = add_partials(v[k], part, nsplit, R, r, d, i);
+            }
             if (OUT::KEEP_H) *reinterpret_cast<float4 *>(h + 4 * i) = v[k];
         }
         ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
@@ -500,30 +506,32 @@ hipError_t launch_embed(bool bf16, const EmbedArgs &args, const void *embed, con
 
 // Many rows and few partial tiles: a wavefront per row (d <= 4096).  Its blocks
 // of eight rows leave units idle below a thousand rows (528 rows, three
-// partial tiles: 21 us, 25 us in blocks of one row, against 17 us).
+// partial tiles: 21 us, 25 us in blocks of one row, against 17 us).  It adds
+// several tiles to H one by one only.
 template <typename TG, typename OUT>
-static hipError_t launch_norm(float *H, const float *part, int nsplit, const TG *gain, int R, int d, float eps, OUT o,
-                              hipStream_t s) {
-    if (R >= 1024 && nsplit <= 3 && d <= 4096) {
+static hipError_t launch_norm(float *H, const float *part, int nsplit, bool sum_first, const TG *gain, int R, int d,
+                              float eps, OUT o, hipStream_t s) {
+    if (R >= 1024 && nsplit <= (sum_first ? 1 : 3) && d <= 4096) {
         kvr_launch((rmsnorm_wave_kernel<TG, OUT, 16>), dim3((R + 7) / 8), dim3(512), 0, s, H, part, nsplit, R, gain, d, eps,
                    o);
     } else {
         const int threads = std::min(1024, (d / 4 + 63) / 64 * 64);
-        kvr_launch((rmsnorm_kernel<TG, OUT>), dim3(R), dim3(threads), 0, s, H, part, nsplit, R, gain, d, eps, o);
+        kvr_launch((rmsnorm_kernel<TG, OUT>), dim3(R), dim3(threads), 0, s, H, part, nsplit, sum_first, R, gain, d, eps, o);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_rmsnorm(bool bf16, float *H, const float *part, int nsplit, const void *gain, int R, int d, float eps,
-                          void *X, void *X_lo, int ldx, bool perm, hipStream_t s) {
+hipError_t launch_rmsnorm(bool bf16, float *H, const float *part, int nsplit, bool sum_first, const void *gain, int R, int d,
+                          float eps, void *X, void *X_lo, int ldx, bool perm, hipStream_t s) {
     if (R <= 0) return hipSuccess;
     if (d % 4 != 0 || d > 4 * 1024 * NORM_V || (!perm && ldx % 4 != 0) || (!bf16 && perm)) return hipErrorInvalidValue;
     if (!bf16)
-        return launch_norm(H, part, nsplit, (const float *)gain, R, d, eps, OperandOut<float, false>{(float *)X, nullptr, ldx}, s);
+        return launch_norm(H, part, nsplit, sum_first, (const float *)gain, R, d, eps,
+                           OperandOut<float, false>{(float *)X, nullptr, ldx}, s);
     if (perm)
-        return launch_norm(H, part, nsplit, (const bf16_t *)gain, R, d, eps,
+        return launch_norm(H, part, nsplit, sum_first, (const bf16_t *)gain, R, d, eps,
                            OperandOut<bf16_t, true>{(bf16_t *)X, (bf16_t *)X_lo, ldx}, s);
-    return launch_norm(H, part, nsplit, (const bf16_t *)gain, R, d, eps,
+    return launch_norm(H, part, nsplit, sum_first, (const bf16_t *)gain, R, d, eps,
                        OperandOut<bf16_t, false>{(bf16_t *)X, (bf16_t *)X_lo, ldx}, s);
 }
 
@@ -543,13 +551,13 @@ hipError_t launch_resid_gain(bool bf16_gain, float *H, const float *part, int ns
     return hipGetLastError();
 }
 
-hipError_t launch_final_norm(bool bf16_gain, float *H, const float *part, int nsplit, const void *gain,
+hipError_t launch_final_norm(bool bf16_gain, float *H, const float *part, int nsplit, bool sum_first, const void *gain,
                              const RowInfo *rows, const DocInfo *docs, int R, int d, float eps, hipStream_t s) {
     if (R <= 0) return hipSuccess;
     if (d % 4 != 0 || d > 4 * 1024 * NORM_V) return hipErrorInvalidValue;
     const HiddenOut o{rows, docs, nullptr, 0};
-    if (bf16_gain) return launch_norm(H, part, nsplit, (const bf16_t *)gain, R, d, eps, o, s);
-    return launch_norm(H, part, nsplit, (const float *)gain, R, d, eps, o, s);
+    if (bf16_gain) return launch_norm(H, part, nsplit, sum_first, (const bf16_t *)gain, R, d, eps, o, s);
+    return launch_norm(H, part, nsplit, sum_first, (const float *)gain, R, d, eps, o, s);
 }
 
 hipError_t launch_rope_scatter(bool bf16, const float *qkv, int nsplit, const void *bq, const void *bk,

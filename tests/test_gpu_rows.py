@@ -114,3 +114,36 @@ def test_rows_do_not_see_later_slots(monkeypatch, dtype, hd, hq, hkv, items):
                 assert relmax(after[l, kv][:, rows], ref[l, kv][:, rows]) <= TOL[dtype]
     finally:
         eng.close()
+
+
+# (dtype, d_model, query / kv heads, head_dim, tokens): K in one slice and in several, with and without a remainder of 16
+# and of 4; both tile sizes of the many-row kernel, the larger one with two slices of odd quarters
+K_ORDERS = [(F32, 256, 4, 4, 64, 1501), (F32, 200, 3, 1, 12, 700), (F32, 1044, 2, 1, 6, 700), (BF16, 268, 4, 2, 12, 700),
+            (F32, 272, 28, 2, 128, 2060), (BF16, 272, 41, 1, 80, 1800)]
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv,hd,n", K_ORDERS, ids=[f"{'bf16' if c[0] else 'f32'}-{c[1]}-{c[5]}" for c in K_ORDERS])
+def test_projection_rows_do_not_depend_on_the_pass(dtype, d, hq, hkv, hd, n):
+    """Keys and values of layer 0 depend on a row's token and position only: CacheBlend's deviations there are exactly
+    zero whether the suffix has a few rows or hundreds, and its rule falls to the lowest positions."""
+    shape = synth.ModelShape(f"generic {d}", 1, d, hq, hkv, hd, 64, 256, 1e-5, 10000.0)
+    w = synth.make_weights(shape, dtype=torch.bfloat16 if dtype == BF16 else torch.float32, seed=d)
+    eng = Engine(shape, to_device_weights(w), dtype, max_ctx=n, max_rows=64)
+    try:
+        toks = synth.make_tokens(n, shape.vocab, seed=1)
+        cache = eng.new_cache(n)
+        say(f"case: {shape.name} prefill n={n}")
+        eng.prefill(toks.cuda(), cache)
+        for rows in (18, 40, 64, 65, 250, 685):
+            s0, K = n - rows, min(8, rows - 5)
+            new = synth.apply_edit(toks, s0, 4, shape.vocab).cuda()
+            out = torch.full((K,), -1, dtype=torch.int32, device="cuda")
+            dev = torch.full((n - 1 - s0 - 4,), -1.0, device="cuda")
+            say(f"case: suffix of {rows} rows")
+            kvr.kvr_select_cacheblend(eng.ctx, cache.data_ptr(), n, n, new.data_ptr(), s0, s0 + 4, K, 0, out.data_ptr(),
+                                      dev.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert torch.count_nonzero(dev).item() == 0, (rows, dev.max().item())
+            assert out.cpu().tolist() == list(range(s0 + 4, s0 + 4 + K))
+    finally:
+        eng.close()
