@@ -26,8 +26,14 @@
 // (a masked key's probability is zero, its product with them would not be) and
 // added afterwards for the rows that see them.
 //
-// What bounds it: the fp32 matrix rate on long contexts (16 instructions of
-// 32 cycles per 16 keys x 16 rows at head_dim 64), latency on short ones.
+// What bounds it: the fp32 matrix rate on long contexts (32 instructions of
+// 32 cycles per 16 keys x 16 rows at head_dim 64), latency on short ones.  The
+// blocks that share a compute unit hide each other's two barriers per key
+// tile, so the registers are bounded for the att_generic_blocks that the
+// planner counts on (146 at 64, 235 at 128; without the bound 174 and 270,
+// which left two and one): 2500-token fp32 prefill, 32 heads of 128, 985 ->
+// 714 us a layer, 1501 tokens, 4 heads of 64, 32 -> 26 us.  Four blocks at 64
+// would spill.
 // Tiny fp32 decoder (4 heads of 64), per layer against the kernel it replaced
 // (one wavefront per row and head, one key per step): 1501-token prefill
 // 1243 -> 36 us, 40-row repair at position 128 96 -> 8 us, plus a combine of
@@ -88,7 +94,8 @@ __device__ __forceinline__ f32x4 load_dims(const bf16_t *p, int d, int hd, bool 
 
 // HDP: head_dim padded to 64 or 128; KG: key groups.
 template <typename T, int HDP, int KG>
-__global__ __launch_bounds__(64 * WAVES) void attention_generic_kernel(const T *Q, const T *Q_lo, const RowInfo *rows,
+__global__ __launch_bounds__(64 * WAVES, att_generic_blocks(HDP)) void attention_generic_kernel(const T *Q, const T *Q_lo,
+                                                                       const RowInfo *rows,
                                                                        const AttnItem *items, int layer, int Hq,
                                                                        int Hkv, int hd, int MT, float *part, T *O,
                                                                        T *O_lo, int o_perm, float *lse) {

@@ -331,6 +331,8 @@ hipError_t launch_copy_rows(const CopySegments &sg, const void *src, size_t src_
 
 // Attention item geometry shared by the planner and the kernels.
 constexpr int ATT_KT = 64;     // keys per LDS tile
+// Blocks of the generic kernel that share a compute unit.
+constexpr int att_generic_blocks(int head_dim) { return head_dim > 64 ? 2 : 3; }
 
 // Four consecutive output dimensions of an attention row (columns c .. c+n-1,
 // n <= 4 of them real; four together when n == 4 and c is a multiple of 4, where

@@ -195,11 +195,11 @@ size_t elem_size(const kvr_dims &d) { return d.dtype == KVR_BF16 ? 2 : 4; }
 // longer combine (Mistral shape, 48 rows at 4900-4950: 0.92 ms of attention
 // and combine per repair at 768 items against 0.64 ms at 256).
 //
-// The generic kernel's blocks are smaller (four wavefronts, 35 KB of LDS at
-// head_dim 64: four to a unit; two at 128), and an item of 64 rows reads each
-// key for all of them: with enough row blocks it keeps them whole and takes
-// key ranges for two to four blocks per unit (1501-token fp32 prefill, 4
-// heads: 235 -> 213 us a call against one-tile items, one per unit).
+// The generic kernel's blocks are smaller (four wavefronts; by registers three
+// to a unit at head_dim 64, two at 128), and an item of 64 rows reads each key
+// for all of them: with enough row blocks it keeps them whole and takes key
+// ranges for as many blocks as the units hold (1501-token fp32 prefill, 4
+// heads: 235 us a call with one-tile items, one per unit, 214 so).
 void plan_attention(const kvr_ctx *c, Tables &t, bool mfma) {
     const int Hkv = c->d.n_kv_heads;
     const int G = c->d.n_heads / Hkv;
@@ -228,7 +228,7 @@ void plan_attention(const kvr_ctx *c, Tables &t, bool mfma) {
     bool split = (long long)blocks.size() * Hkv < target / 2;
     if (!mfma && target_env <= 0 && (long long)blocks.size() * Hkv >= 64) {
         const int per_item = (G * mt + 3) / 4;  // blocks of an item (a wavefront per (head, row tile) pair)
-        target = std::max(1, 256 * (c->d.head_dim > 64 ? 2 : 4) / per_item);
+        target = std::max(1, 256 * att_generic_blocks(c->d.head_dim) / per_item);
         split = (long long)blocks.size() * Hkv < target / 2;
     } else if (split) {
         mt = std::min(mt_max, std::max(1, env_int("KVR_ATT_MT", 1)));
