@@ -21,7 +21,9 @@
 // per item the wavefronts split into KG key groups that take alternate 16-key
 // tiles and merge their softmax states in LDS at the end.
 //
-// A row depends on no slot behind its position, whatever that slot holds: in
+// A row's result depends on the key ranges of its item, which follow from the
+// rows of the whole pass, and on nothing else of the rows beside it.  It
+// depends on no slot behind its position, whatever that slot holds: in
 // the tiles that have a mask, values that are not finite are staged as zeros
 // (a masked key's probability is zero, its product with them would not be) and
 // added afterwards for the rows that see them.
@@ -213,7 +215,7 @@ __global__ __launch_bounds__(64 * WAVES, att_generic_blocks(HDP)) void attention
             }
         mx = xmax4(mx);
         if (__any(mx > m + RESCALE_SLACK)) {
-            const float mnew = fmaxf(m, mx);
+            const float mnew = mx > m + RESCALE_SLACK ? mx : m;  // the other rows of the tile keep theirs
             const float corr = m == -INFINITY ? 0.f : exp2f(m - mnew);
             m = mnew;
             l *= corr;

@@ -147,3 +147,35 @@ def test_projection_rows_do_not_depend_on_the_pass(dtype, d, hq, hkv, hd, n):
             assert out.cpu().tolist() == list(range(s0 + 4, s0 + 4 + K))
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv,hd,n", [(F32, 256, 4, 4, 64, 1100), (F32, 200, 6, 2, 12, 700), (BF16, 268, 4, 1, 20, 700)],
+                         ids=["f32-256", "f32-200", "bf16-268"])
+def test_rows_do_not_depend_on_the_rows_beside_them(monkeypatch, dtype, d, hq, hkv, hd, n):
+    """With whole key ranges for every row (no split of the attention), rows recomputed over the cache of a prefill of the
+    same tokens are that prefill's bit for bit, every layer and the hidden rows, whether few or hundreds: the projections
+    add up K alike for every row count, and no step looks at a row's neighbours."""
+    monkeypatch.setenv("KVR_ATT_TARGET", "1")
+    shape = synth.ModelShape(f"rows {d}", 2, d, hq, hkv, hd, 4 * d + 24, 256, 1e-5, 10000.0)
+    w = synth.make_weights(shape, dtype=torch.bfloat16 if dtype == BF16 else torch.float32, seed=d)
+    for lw in w["layers"]:
+        lw["wq"] *= 100  # scores spread over tens, so that rows raise their running maxima at different keys
+    eng = Engine(shape, to_device_weights(w), dtype, max_ctx=n, max_rows=n)
+    try:
+        toks = synth.make_tokens(n, shape.vocab, seed=1).cuda()
+        cache, full = eng.new_cache(n), torch.zeros((n, shape.d_model), device="cuda")
+        say(f"case: {shape.name} prefill n={n}")
+        eng.prefill(toks, cache, full)
+        rng = np.random.default_rng(d)
+        for extra in (0, 40, 61, 62, 300, n - 4):
+            pool = np.setdiff1d(np.arange(n - 1), [100, 101, 102])
+            A = sorted(rng.choice(pool, size=min(extra, len(pool)), replace=False).tolist())
+            P = od.repaired_set(100, 103, A)
+            again, out = cache.clone(), torch.zeros((len(P), shape.d_model), device="cuda")
+            say(f"case: {len(P)} rows")
+            eng.repair([dict(cache=again, tokens=toks, edit_start=100, edit_end=103, positions=A, hidden=out)])
+            torch.cuda.synchronize()
+            assert torch.equal(again, cache), (len(P), (again - cache).abs().max().item())
+            assert torch.equal(out, full[P]), (len(P), (out - full[P]).abs().max().item())
+    finally:
+        eng.close()
