@@ -27,6 +27,12 @@
  *   valid once the stream has reached that point.  Calls on one context use
  *   the context's workspace and must be ordered (one stream, or synchronised
  *   by the caller); one context per host thread.
+ * - A call whose stream is being captured into a HIP graph puts its tables
+ *   (positions, document descriptions, plans) into the graph: a replay repeats
+ *   that call on the same device buffers, whatever the context did in between.
+ *   A replay uses the context's workspace and is ordered like a call.  What a
+ *   call allocates on first use (kvr_score, kvr_generate, the GPU selectors)
+ *   must have been allocated by an earlier call.
  * - Arguments are validated before anything is enqueued: on any status other
  *   than KVR_OK or KVR_E_HIP, no GPU work was enqueued and no cache was
  *   touched.  KVR_E_HIP means a HIP call failed after enqueueing began; cache

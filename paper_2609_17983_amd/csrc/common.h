@@ -202,6 +202,13 @@ struct EmbedArgs {
 };
 hipError_t launch_embed(bool bf16, const EmbedArgs &args, const void *embed, const void *gain, int d, int vocab, float *H,
                         void *X, void *X_lo, float *ssq, hipStream_t s);
+// A piece of a captured pass's tables: the bytes travel in the kernel argument
+// (HIP's limit is 4 KB), so that a graph holds them itself.
+struct TableChunk {
+    u32x4 data[224];
+    int32_t n16;  // 16-byte units used
+};
+hipError_t launch_table_chunk(const TableChunk &chunk, void *dst, hipStream_t s);
 // RMSNorm of the residual rows.  First H[r] += sum of `nsplit` fp32 partial
 // tiles part[s][R][d] (the split-K outputs of the projection that produced the
 // residual update; nsplit 0 = none), then X = H * rsqrt(mean(H^2)+eps) * gain,

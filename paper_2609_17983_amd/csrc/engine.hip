@@ -183,6 +183,17 @@ struct DeviceGuard {
     }
 };
 
+// Whether work on `s` is being captured into a graph.  (For the null stream
+// the query fails while another stream is captured; its work is not captured.)
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
+}
+
 bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 size_t elem_size(const kvr_dims &d) { return d.dtype == KVR_BF16 ? 2 : 4; }
@@ -510,22 +521,40 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
     const size_t o_comb = o_items + align_up(t.items.size() * sizeof(AttnItem), 256);
     const size_t total = o_comb + t.comb.size() * sizeof(CombineItem);
     if (total > c->tables_bytes) return fail(c, KVR_E_RANGE, "pass tables exceed the context's staging capacity");
-    if (c->stage_pending) {
-        hipError_t e = hipEventSynchronize(c->stage_ev);
-        if (e != hipSuccess) return hip_fail(c, e, "hipEventSynchronize(staging)");
-        c->stage_pending = false;
-    }
-    memcpy(c->h_stage, t.rows.data(), t.rows.size() * sizeof(RowInfo));
-    memcpy(c->h_stage + o_docs, t.docs.data(), t.docs.size() * sizeof(DocInfo));
-    if (!t.items.empty()) memcpy(c->h_stage + o_items, t.items.data(), t.items.size() * sizeof(AttnItem));
-    if (!t.comb.empty()) memcpy(c->h_stage + o_comb, t.comb.data(), t.comb.size() * sizeof(CombineItem));
+    const struct { const void *p; size_t off, bytes; } parts[4] = {
+        {t.rows.data(), 0, t.rows.size() * sizeof(RowInfo)}, {t.docs.data(), o_docs, t.docs.size() * sizeof(DocInfo)},
+        {t.items.data(), o_items, t.items.size() * sizeof(AttnItem)}, {t.comb.data(), o_comb, t.comb.size() * sizeof(CombineItem)}};
+    hipError_t e = hipSuccess;
     // Small tables are uploaded by the pass's first kernel, larger ones by a
     // copy in front of it (a kernel's reads of host memory are slower than the
-    // copy engine's once latency no longer dominates).
-    const bool by_kernel = total <= UPLOAD_BY_KERNEL;
-    hipError_t e = hipSuccess;
-    if (!by_kernel) e = hipMemcpyAsync(c->d_tables, c->h_stage, total, hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync(tables)");
+    // copy engine's once latency no longer dominates).  A captured pass must
+    // not read the staging buffer, which the context's next call overwrites:
+    // its tables go into the graph as kernel arguments.
+    const bool captured = capturing(s);
+    const bool by_kernel = !captured && total <= UPLOAD_BY_KERNEL;
+    if (captured) {
+        TableChunk chunk;
+        for (size_t b = 0; b < total; b += sizeof(chunk.data)) {
+            const size_t end = std::min(total, b + sizeof(chunk.data));
+            for (const auto &q : parts) {
+                const size_t lo = std::max(b, q.off), hi = std::min(end, q.off + q.bytes);
+                if (lo < hi) memcpy((char *)chunk.data + (lo - b), (const char *)q.p + (lo - q.off), hi - lo);
+            }
+            chunk.n16 = (int32_t)((end - b + 15) / 16);
+            e = launch_table_chunk(chunk, c->d_tables + b, s);
+            if (e != hipSuccess) return hip_fail(c, e, "table upload");
+        }
+    } else {
+        if (c->stage_pending) {
+            e = hipEventSynchronize(c->stage_ev);
+            if (e != hipSuccess) return hip_fail(c, e, "hipEventSynchronize(staging)");
+            c->stage_pending = false;
+        }
+        for (const auto &q : parts)
+            if (q.bytes) memcpy(c->h_stage + q.off, q.p, q.bytes);
+        if (!by_kernel) e = hipMemcpyAsync(c->d_tables, c->h_stage, total, hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync(tables)");
+    }
     const RowInfo *rows = (const RowInfo *)c->d_tables;
     const DocInfo *docs = (const DocInfo *)(c->d_tables + o_docs);
     const AttnItem *items = (const AttnItem *)(c->d_tables + o_items);
@@ -577,9 +606,11 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
     KVR_CHECK(launch_embed(bf, ea, c->embed, first_gain ? c->layers[0].attn_norm : nullptr, D, d.vocab, c->H, c->Xn,
                            c->Xn_lo, c->rs_ssq, s), "embed", ST_EMBED);
     // the staging buffer is free once the copy or the first kernel is through
-    e = hipEventRecord(c->stage_ev, s);
-    if (e != hipSuccess) return hip_fail(c, e, "hipEventRecord(staging)");
-    c->stage_pending = true;
+    if (!captured) {
+        e = hipEventRecord(c->stage_ev, s);
+        if (e != hipSuccess) return hip_fail(c, e, "hipEventRecord(staging)");
+        c->stage_pending = true;
+    }
     int resid_split = 0;  // partial tiles in P still to be added to H
     const int n_run = kv_layer >= 0 ? kv_layer + 1 : d.n_layers;
     for (int l = 0; l < n_run; ++l) {

@@ -378,6 +378,10 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a, const TW *embed
     }
 }
 
+__global__ __launch_bounds__(256) void table_chunk_kernel(TableChunk c, u32x4 *dst) {
+    if ((int)threadIdx.x < c.n16) dst[threadIdx.x] = c.data[threadIdx.x];
+}
+
 // Four values of row-major type T at p (8-byte or 16-byte store).
 template <typename T>
 __device__ __forceinline__ void store4(T *p, float4 v) {
@@ -501,6 +505,12 @@ hipError_t launch_embed(bool bf16, const EmbedArgs &args, const void *embed, con
     else
         kvr_launch((embed_kernel<float, false>), grid, dim3(256), 0, s, a, (const float *)embed, (const float *)nullptr, d,
                    vocab, H, (bf16_t *)nullptr, (bf16_t *)nullptr, (float *)nullptr);
+    return hipGetLastError();
+}
+
+hipError_t launch_table_chunk(const TableChunk &chunk, void *dst, hipStream_t s) {
+    if (chunk.n16 < 1 || chunk.n16 > (int)(sizeof(chunk.data) / 16)) return hipErrorInvalidValue;
+    kvr_launch(table_chunk_kernel, dim3(1), dim3(256), 0, s, chunk, (u32x4 *)dst);
     return hipGetLastError();
 }
 

@@ -159,8 +159,8 @@ def test_tiled_row_tiles(monkeypatch, rt):
 # documents, more rows than the argument holds), or finds them on the device (tables too large to be uploaded by it)
 @pytest.mark.parametrize("K,docs", [(20, 1), (20, 3), (300, 1), (1500, 3)], ids=["argument", "documents", "rows", "copied"])
 def test_pass_tables_and_graph_replay(K, docs):
-    """A repair captured into a graph (relaxed mode) and replayed, with eager repairs of the same edits and
-    synchronisations between the replays: every replay equals the eager result bit for bit."""
+    """A repair captured into a graph (relaxed mode) and replayed, with eager repairs of the same edits (the same tables)
+    and synchronisations between the replays: every replay equals the eager result bit for bit."""
     shape = synth.ModelShape("tables", 2, 256, 4, 2, 64, 256, 256, 1e-5, 10000.0)
     n = 2000
     w = synth.make_weights(shape, dtype=torch.bfloat16, seed=3)
@@ -198,6 +198,56 @@ def test_pass_tables_and_graph_replay(K, docs):
             eng.repair(jobs)
             torch.cuda.synchronize()
             assert all(torch.equal(a, b) for a, b in zip(hidden, want)), f"eager after replay {k}"
+        del g
+    finally:
+        eng.close()
+
+
+@pytest.mark.parametrize("K,docs", [(20, 1), (20, 3), (300, 1), (1500, 3)], ids=["argument", "documents", "rows", "copied"])
+def test_graph_replay_after_other_work(K, docs):
+    """Between the replays the context repairs another document at other positions, as many rows and fewer: a replay
+    repeats the captured call on its own buffers and leaves the other cache alone."""
+    shape = synth.ModelShape("tables", 2, 256, 4, 2, 64, 256, 256, 1e-5, 10000.0)
+    n = 2000
+    w = synth.make_weights(shape, dtype=torch.bfloat16, seed=3)
+    eng = Engine(shape, to_device_weights(w), BF16, max_ctx=n, max_rows=docs * (K + 16))
+    try:
+        def job(i, at, count, seed):
+            return dict(cache=synth.make_stale_cache(shape, n, label=i).cuda(), tokens=synth.make_tokens(n, shape.vocab, seed=i).cuda(),
+                        edit_start=at, edit_end=at + 16, positions=osel.select_random(n, at, at + 16, count, seed),
+                        hidden=torch.zeros((count + 16, shape.d_model), device="cuda"))
+
+        def state(jobs):
+            torch.cuda.synchronize()
+            return [x.clone() for j in jobs for x in (j["cache"], j["hidden"])]
+
+        def reset(jobs, start):
+            for x, v in zip((x for j in jobs for x in (j["cache"], j["hidden"])), start):
+                x.copy_(v)
+
+        jobs = [job(i, 100, K, 1) for i in range(docs)]
+        others = [[job(10 + i, 400, K, 2) for i in range(docs)], [job(20, 700, K // 2, 3)]]
+        start, ostart = state(jobs), [state(o) for o in others]
+        say(f"case: eager repairs of {docs} x {K + 16} rows")
+        eng.repair(jobs)
+        want = state(jobs)
+        owant = []
+        for o in others:
+            eng.repair(o)
+            owant.append(state(o))
+        say("case: captured repair")
+        g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.graph(g, stream=side, capture_error_mode="relaxed"):
+            eng.repair(jobs)
+        for k in range(4):
+            for o, ow, os_ in zip(others, owant, ostart):
+                reset(jobs, start)
+                reset(o, os_)
+                eng.repair(o)
+                g.replay()
+                assert all(torch.equal(a, b) for a, b in zip(state(jobs), want)), f"replay {k}"
+                assert all(torch.equal(a, b) for a, b in zip(state(o), ow)), f"other document after replay {k}"
         del g
     finally:
         eng.close()
