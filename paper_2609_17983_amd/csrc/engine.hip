@@ -527,7 +527,10 @@ kvr_status run_pass(kvr_ctx *c, Tables &t, hipStream_t s, int kv_layer = -1, con
     hipError_t e = hipSuccess;
     // Small tables are uploaded by the pass's first kernel, larger ones by a
     // copy in front of it (a kernel's reads of host memory are slower than the
-    // copy engine's once latency no longer dominates).  A captured pass must
+    // copy engine's once latency no longer dominates): 600 rows of the tiny
+    // fp32 model, one layer, 76 us a call against 90 with the copy, 1501 rows
+    // 119 against 126, 300 rows of a Qwen-shaped layer 387 against 402; 4000
+    // rows 262 against 257.  A captured pass must
     // not read the staging buffer, which the context's next call overwrites:
     // its tables go into the graph as kernel arguments.
     const bool captured = capturing(s);

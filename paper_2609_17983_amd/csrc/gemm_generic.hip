@@ -320,7 +320,9 @@ __global__ __launch_bounds__(256, 2) void linear_generic_tiled_kernel(LinearArgs
 }
 
 // Output tiles of a tiled launch: 128 x 128 when there are two for every
-// compute unit, else 64 x 64.
+// compute unit, else 64 x 64.  fp32 prefills of one layer, with the line at
+// 256, 512 and 1024 tiles: d_model 2048, 2500 tokens 3524, 3130, 3133 us;
+// d_model 4096, 2000 tokens 7845, 7849, 8170 us.
 int generic_tile(int R, int vcols) {
     return (long long)((R + 127) / 128) * ((vcols + 127) / 128) >= 512 ? 4 : 2;
 }
@@ -360,7 +362,9 @@ hipError_t launch_epi(const LinearArgs &a, hipStream_t s) {
 // per compute unit for a row block of 64, and slices of 256 k, or of 128 while
 // those are no more than four (tiny fp32 decoder, 600-token prefill: 136 us a
 // call against 152 with slices of 256 only, which leave a 256-wide projection
-// to 40 blocks; its 40-row repair takes 101-104 us either way).
+// to 40 blocks; its 40-row repair takes 101-104 us either way).  At most eight:
+// an 8192-wide projection to 1024 columns in a layer of 300 rows, 265 us with
+// four, 246 with eight, 246 with sixteen; 40 rows 96, 98 and 98 us.
 int generic_slices(int N, int K) {
     return std::max(1, std::min({512 / ((N + 15) / 16), std::max(std::min(K / 128, 4), K / 256), 8}));
 }

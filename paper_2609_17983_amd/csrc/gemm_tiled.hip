@@ -304,13 +304,15 @@ int output_tiles(int R, int vrows, int mt) {
 // a partial tile past the first is written and read back.  A last round that
 // fills part of the units costs about half of what it would on paper (the
 // chip is power bound and the units that have work clock higher), hence the
-// average of the two.  EFF is the measured time per row tile (Llama-3-8B
-// gate/up at 5000 rows, us per row tile and round: 12.4, 12.3, 11.8, 12.8,
-// 12.1 for 4 .. 8 row tiles; six leave room for three blocks per unit, seven
-// and eight for two).  Measured against the former rule (256-, 128- or 64-row
-// blocks by grid size; us, same box): batched repair (3072 rows) Q/K/V, six
-// row tiles, one full round: 272 -> 220; Qwen2.5-7B down projection at 528
-// rows, six row tiles x split 3 instead of four x 5: 139 -> 129.
+// average of the two.  EFF is the time per row tile against six of them:
+// measured (Llama-3-8B gate/up at 5000 rows) 12.4, 12.3, 11.8, 12.8, 12.1 us
+// per row tile and round for 4 .. 8, that is 1.05, 1.04, 1, 1.08, 1.03, and
+// entered 0.01 to 0.02 lower, by which boxes differ; six leave room for three
+// blocks per unit, seven and eight for two.  Measured against the former rule
+// (256-, 128- or 64-row blocks by grid size; us, same box): batched repair
+// (3072 rows) Q/K/V, six row tiles, one full round: 272 -> 220; Qwen2.5-7B down
+// projection at 528 rows, six row tiles x split 3 instead of four x 5: 139 ->
+// 129.
 // KVR_TILED_RT (4 .. 8; larger values stand for 8) forces the row tiles.
 TiledPlan plan_tiled(int R, int vrows, int K, bool split_ok, size_t p_floats) {
     static const double EFF[MT_MAX + 1] = {0, 0, 0, 0, 1.04, 1.03, 1.0, 1.06, 1.01};

@@ -1,5 +1,5 @@
-// Row kernels of the scoring forward: the log-softmax over the vocabulary with the teacher-forced target gather and
-// the greedy argmax.
+// Row kernels of the scoring forward: the log-softmax over the vocabulary with
+// the teacher-forced target gather and the greedy argmax.
 #include <math.h>
 
 #include <algorithm>

@@ -612,13 +612,11 @@ def test_bf16_generic_kernels_forced(monkeypatch):
     _prefill_then_repair(MID, kvr.KVR_BF16, 300, 15, (100, 116), "mid-bf16 generic kernels")
 
 
-@pytest.mark.parametrize("rt", ["16", "8", "4"])
+@pytest.mark.parametrize("rt", ["8", "7", "6", "5", "4"])
 def test_wide_prefill_forced_row_blocks(monkeypatch, rt):
-    """Each of the tiled kernel's row-block shapes forced on the 1100-row
-    prefill (69 row tiles of 16): 256 rows (eight wavefronts, three LDS
-    stages; the launcher picks it only for grids of eight rounds or more),
-    128 rows (two stages, two blocks per compute unit) and 64 rows; the last
-    row block is partial in each."""
+    """Each of the tiled kernel's block heights, four to eight 16-row tiles,
+    forced on the 1100-row prefill (69 row tiles, the last of 12 rows): the
+    last row block is partial in each."""
     monkeypatch.setenv("KVR_TILED_RT", rt)
     shape, n = WIDE, 1100
     w = synth.make_weights(shape, dtype=torch.bfloat16, seed=11)
