@@ -251,6 +251,10 @@ int attention_max_row_tiles(int Hq, int Hkv);
 hipError_t launch_attention_mfma(const bf16_t *Q, const bf16_t *Q_lo, const RowInfo *rows,
                                  const AttnItem *items, int n_items, int MT, int layer, int Hq, int Hkv, int hd,
                                  float *part, bf16_t *O, bf16_t *O_lo, bool o_perm, float *lse, hipStream_t s);
+// The 64-wide part of it (attention64.hip), behind launch_attention_mfma's checks.
+hipError_t launch_attention_mfma64(const bf16_t *Q, const bf16_t *Q_lo, const RowInfo *rows, const AttnItem *items,
+                                   int n_items, int MT, int layer, int Hq, int Hkv, float *part, bf16_t *O, bf16_t *O_lo,
+                                   bool o_perm, float *lse, hipStream_t s);
 hipError_t launch_attention_combine(bool bf16, const CombineItem *items, int n_items, int MT, const float *part, int Hq,
                                     int Hkv, int hd, void *O, void *O_lo, bool o_perm, float *lse, hipStream_t s);
 // Any R, N, K, fp32 or bf16, row-major operands (a.w).  A STORE output is the
