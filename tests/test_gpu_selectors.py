@@ -76,8 +76,9 @@ def test_cacheblend_mid_bf16():
 def test_cacheblend_first_layer_sees_no_deviation():
     """At layer 0 a pool position's keys/values depend only on its own token
     and position, which an in-place edit leaves unchanged: the deviation is
-    exactly zero (same kernels, row-independent), so the rule degenerates to
-    the lowest positions (EditLocal's window)."""
+    exactly zero (the prefill's and the suffix's passes cut K into the same
+    slices at these sizes), so the rule degenerates to the lowest positions
+    (EditLocal's window)."""
     shape, n, s0, span, K = MID, 700, 300, 16, 48
     w = synth.make_weights(shape, dtype=torch.bfloat16)
     eng = Engine(shape, to_device_weights(w), kvr.KVR_BF16, max_ctx=n, max_rows=64)
