@@ -117,9 +117,9 @@ def test_rows_do_not_see_later_slots(monkeypatch, dtype, hd, hq, hkv, items):
 
 
 # (dtype, d_model, query / kv heads, head_dim, tokens): K in one slice and in several, with and without a remainder of 16
-# and of 4; both tile sizes of the many-row kernel, the larger one with two slices of odd quarters
+# and of 4; both tile sizes of the many-row kernel, the larger one with two slices (added up in memory) in both types
 K_ORDERS = [(F32, 256, 4, 4, 64, 1501), (F32, 200, 3, 1, 12, 700), (F32, 1044, 2, 1, 6, 700), (BF16, 268, 4, 2, 12, 700),
-            (F32, 272, 28, 2, 128, 2060), (BF16, 272, 41, 1, 80, 1800)]
+            (F32, 272, 28, 2, 128, 2060), (BF16, 272, 46, 2, 80, 2060), (BF16, 272, 41, 1, 80, 1800)]
 
 
 @pytest.mark.parametrize("dtype,d,hq,hkv,hd,n", K_ORDERS, ids=[f"{'bf16' if c[0] else 'f32'}-{c[1]}-{c[5]}" for c in K_ORDERS])

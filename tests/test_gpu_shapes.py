@@ -253,6 +253,47 @@ def test_graph_replay_after_other_work(K, docs):
         eng.close()
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
+def test_graph_of_several_passes(dtype):
+    """One call that makes many passes (a query block, then a pass per generated token), captured and replayed between
+    eager repairs on the same context: each pass keeps its own tables."""
+    shape = synth.ModelShape("generate", 2, 256, 4, 2, 64, 256, 256, 1e-5, 10000.0)
+    n, q, new = 300, 20, 6
+    w = synth.make_weights(shape, dtype=torch.bfloat16 if dtype == BF16 else torch.float32, seed=3)
+    eng = Engine(shape, to_device_weights(w), dtype, max_ctx=512, max_rows=64)
+    try:
+        toks = synth.make_tokens(n + q + new, shape.vocab, seed=7).cuda()
+        toks[n + q:] = -1
+        cache = eng.new_cache(512)
+        eng.prefill(toks, cache, n=n)
+        other, otoks = cache.clone(), synth.make_tokens(n, shape.vocab, seed=8).cuda()
+        start, tstart = cache.clone(), toks.clone()
+
+        def generate():
+            kvr.kvr_generate(eng.ctx, cache.data_ptr(), n, 512, toks.data_ptr(), q, new, torch.cuda.current_stream().cuda_stream)
+
+        say("case: eager generation")
+        generate()
+        torch.cuda.synchronize()
+        want, twant = cache.clone(), toks.clone()
+        assert (twant[n + q:] >= 0).all()
+        say("case: captured generation")
+        g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.graph(g, stream=side, capture_error_mode="relaxed"):
+            generate()
+        for k in range(4):
+            cache.copy_(start)
+            toks.copy_(tstart)
+            eng.repair([dict(cache=other, tokens=otoks, edit_start=10 + k, edit_end=20 + k, positions=[40, 50, 60], n=n)])
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(toks, twant) and torch.equal(cache, want), f"replay {k}"
+        del g
+    finally:
+        eng.close()
+
+
 @pytest.mark.parametrize("dtype,hd,hq,hkv", [(F32, 64, 4, 4), (F32, 128, 8, 4), (BF16, 80, 12, 4)],
                          ids=["f32-64", "f32-128", "bf16-80"])
 def test_generic_attention_many_rows(dtype, hd, hq, hkv):
